@@ -239,7 +239,8 @@ moe_status_t moe_combine(const float* y_rows, const int32_t* dest_row, const flo
  * moe_expert_ffn -> moe_combine on one stream, with the same arithmetic and
  * bit-identical results (the FP8 routed-expert FFN of System Design, run
  * from device memory), in fewer launches:
- *   T <= 256: quantization and the slot sort run as one launch;
+ *   quantization and the slot sort run as one launch (T <= 256) or two, which
+ *   also write the prefill GEMMs' tile table;
  *   DECODE regime with T * k <= 16 and I <= 2048: the down projection and
  *   the combine run as one launch (a workgroup computes 16 output columns
  *   for every active expert and combines them per token in LDS);

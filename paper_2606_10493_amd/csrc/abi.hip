@@ -56,13 +56,16 @@ moe_status_t run_ffn_decode_down_combine_one_token(const moe_dims_t& d, const fl
 
 moe_status_t launch_layer_prologue(const uint16_t* x, int32_t T, int32_t H, const int32_t* topk_ids, int32_t k,
                                    int32_t E, uint8_t* qx, float* sx, int32_t* offsets, int32_t* sorted_src,
-                                   int32_t* dest_row, int32_t* dev_status, hipStream_t stream);
+                                   int32_t* dest_row, int32_t* dev_status, const TilesOut& tiles, void* perm_ws,
+                                   hipStream_t stream);
+bool layer_prologue_writes_tiles(int32_t T, int32_t k);
+TilesOut prefill_tiles_out(const moe_dims_t& d, int32_t T, int32_t* tiles);
 
 moe_status_t run_ffn_prefill(const moe_dims_t& d, int32_t T, const uint8_t* qx, const float* sx,
                              const int32_t* offsets, const int32_t* sorted_src, const uint8_t* w_gate,
                              const float* s_gate, const uint8_t* w_up, const float* s_up, const uint8_t* w_down,
                              const float* s_down, float* y_rows, uint8_t* qh, float* sh, int32_t* tiles,
-                             hipStream_t stream);
+                             bool tiles_ready, hipStream_t stream);
 
 size_t prefill_tile_workspace(const moe_dims_t& d, int32_t T);
 moe_status_t prefill_shape_check(const moe_dims_t& d);
@@ -152,7 +155,7 @@ extern "C" moe_status_t moe_expert_ffn(moe_dims_t d, int32_t T, moe_regime_t reg
     return run_ffn_decode(d, T, qx, sx, expert_offsets, sorted_src, w_gate, s_gate, w_up, s_up, w_down, s_down,
                           y_rows, reinterpret_cast<float*>(rest), qh, sh, stream);
   return run_ffn_prefill(d, T, qx, sx, expert_offsets, sorted_src, w_gate, s_gate, w_up, s_up, w_down, s_down, y_rows,
-                         qh, sh, reinterpret_cast<int32_t*>(rest), stream);
+                         qh, sh, reinterpret_cast<int32_t*>(rest), false, stream);
 }
 
 extern "C" size_t moe_expert_ffn_w8a16_workspace(moe_dims_t d, int32_t T) {
@@ -269,30 +272,32 @@ extern "C" moe_status_t moe_ffn_layer(moe_dims_t d, int32_t T, moe_regime_t regi
     return run_ffn_decode_down_combine_one_token(d, h, topk_ids, w_down, s_down, topk_w, out_bf16, stream);
   }
 
-  // Quantize and sort: one launch for a single chunk of tokens.
-  if (T <= 256) {
-    st = launch_layer_prologue(x_bf16, T, d.hidden, topk_ids, d.topk, d.n_experts, qx, sx, offsets, sorted_src,
-                               dest_row, dev_status, stream);
-  } else {
-    st = moe_quant_act(x_bf16, T, d.hidden, qx, sx, stream);
-    if (st == MOE_OK)
-      st = moe_permute(topk_ids, T, d.topk, d.n_experts, offsets, sorted_src, dest_row, dev_status, b + L.perm,
-                       moe_permute_workspace(T, d.topk, d.n_experts), stream);
-  }
+  // Quantize and sort; in the prefill regime the sort also writes the m-tile
+  // table of the GEMMs.
+  uint8_t* qh = b + L.ffn;
+  float* sh = reinterpret_cast<float*>(qh + align256(R * d.inter));
+  uint8_t* rest = reinterpret_cast<uint8_t*>(sh) + align256(R * (d.inter / kBlock) * sizeof(float));
+  const bool tiles_ready = rg == MOE_REGIME_PREFILL && layer_prologue_writes_tiles(T, d.topk);
+  st = launch_layer_prologue(x_bf16, T, d.hidden, topk_ids, d.topk, d.n_experts, qx, sx, offsets, sorted_src, dest_row,
+                             dev_status,
+                             tiles_ready ? prefill_tiles_out(d, T, reinterpret_cast<int32_t*>(rest)) : TilesOut{},
+                             b + L.perm, stream);
   if (st != MOE_OK) return st;
 
   if (rg == MOE_REGIME_DECODE && decode_down_combine_fits(d, T)) {
     // Gate/up, then the down projection and the combine in one launch (the
     // fp32 expert rows stay in LDS).
-    uint8_t* qh = b + L.ffn;
-    float* sh = reinterpret_cast<float*>(qh + align256(R * d.inter));
-    float* h = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(sh) + align256(R * (d.inter / kBlock) * sizeof(float)));
+    float* h = reinterpret_cast<float*>(rest);
     st = run_ffn_decode_gateup(d, T, qx, sx, offsets, sorted_src, w_gate, s_gate, w_up, s_up, h, stream);
     if (st != MOE_OK) return st;
     return run_ffn_decode_down_combine(d, T, h, offsets, w_down, s_down, dest_row, topk_w, out_bf16, stream);
   }
-  st = moe_expert_ffn(d, T, rg, qx, sx, offsets, sorted_src, w_gate, s_gate, w_up, s_up, w_down, s_down, y,
-                      b + L.ffn, moe_expert_ffn_workspace(d, T, rg), stream);
+  if (rg == MOE_REGIME_DECODE)
+    st = run_ffn_decode(d, T, qx, sx, offsets, sorted_src, w_gate, s_gate, w_up, s_up, w_down, s_down, y,
+                        reinterpret_cast<float*>(rest), qh, sh, stream);
+  else
+    st = run_ffn_prefill(d, T, qx, sx, offsets, sorted_src, w_gate, s_gate, w_up, s_up, w_down, s_down, y, qh, sh,
+                         reinterpret_cast<int32_t*>(rest), tiles_ready, stream);
   if (st != MOE_OK) return st;
   return moe_combine(y, dest_row, topk_w, T, d.topk, d.hidden, out_bf16, stream);
 }

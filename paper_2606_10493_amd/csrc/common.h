@@ -294,6 +294,17 @@ struct PrefillRows {
   int32_t tokens;       // activation rows of the gate/up projections (all chunks)
   int64_t rows;         // sorted rows of all chunks (activation rows of the down projection)
   int64_t max_mtiles;   // bound on the launch's 128-row m-tiles (sizes the grid and the descriptor table)
+  bool tiles_ready;     // the m-tile table is written already (one chunk only)
+};
+
+// Expert rows per prefill m-tile, and the m-tile table of a launch over one
+// chunk of rows (see prefill_tiles_kernel): written by the layer's sort, which
+// knows the experts' counts, or by prefill_tiles_kernel.
+constexpr int kPrefillTileRows = 128;
+struct TilesOut {
+  int32_t* mtile_start;  // [E+1]; NULL: no table wanted
+  int4* desc;            // [max_mtiles]
+  int64_t max_mtiles;
 };
 
 void set_error(const char* fmt, ...);

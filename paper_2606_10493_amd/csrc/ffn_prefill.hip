@@ -55,7 +55,7 @@ namespace moe {
 
 namespace {
 
-constexpr int kBM = 128;                // expert rows (tokens) per tile
+constexpr int kBM = kPrefillTileRows;   // expert rows (tokens) per tile
 constexpr int kBN = 256;                // weight rows per tile
 constexpr int kThreads = 512;           // 8 waves x 32 weight rows
 constexpr int kLdsRow = kBlock;         // LDS row (bytes); 16-byte chunks XOR-swizzled, see swz()
@@ -724,10 +724,13 @@ moe_status_t run_ffn_prefill_view(const moe_dims_t& d, const PrefillRows& r, con
   int4* desc = reinterpret_cast<int4*>(tb + tiles_desc_offset(r.n_units));
   int32_t* row_pos = nullptr;
   int32_t* row_tok = nullptr;
-  MOE_LAUNCH("prefill_tiles", prefill_tiles_kernel, dim3(1), dim3(1024), 0, stream, r.offsets, r.off_stride,
-             r.n_units, r.n_chunks, tiles, vstart, desc, r.max_mtiles);
-  moe_status_t st = check_launch("prefill_tiles");
-  if (st != MOE_OK) return st;
+  moe_status_t st = MOE_OK;
+  if (!r.tiles_ready) {
+    MOE_LAUNCH("prefill_tiles", prefill_tiles_kernel, dim3(1), dim3(1024), 0, stream, r.offsets, r.off_stride,
+               r.n_units, r.n_chunks, tiles, vstart, desc, r.max_mtiles);
+    st = check_launch("prefill_tiles");
+    if (st != MOE_OK) return st;
+  }
   if (r.n_chunks > 1) {
     row_pos = reinterpret_cast<int32_t*>(reinterpret_cast<uint8_t*>(desc) + (size_t)r.max_mtiles * sizeof(int4));
     row_tok = row_pos + ((r.rows + 3) & ~(int64_t)3);
@@ -758,15 +761,22 @@ moe_status_t run_ffn_prefill_view(const moe_dims_t& d, const PrefillRows& r, con
   return launch_prefill<false>(dn, r.max_mtiles, stream);
 }
 
+// The m-tile table inside a resident layer's tiles workspace.
+TilesOut prefill_tiles_out(const moe_dims_t& d, int32_t T, int32_t* tiles) {
+  return TilesOut{tiles, reinterpret_cast<int4*>(reinterpret_cast<uint8_t*>(tiles) + tiles_desc_offset(d.n_experts)),
+                  prefill_max_mtiles((int64_t)T * d.topk, d.n_experts)};
+}
+
 moe_status_t run_ffn_prefill(const moe_dims_t& d, int32_t T, const uint8_t* qx, const float* sx,
                              const int32_t* offsets, const int32_t* sorted_src, const uint8_t* w_gate,
                              const float* s_gate, const uint8_t* w_up, const float* s_up, const uint8_t* w_down,
                              const float* s_down, float* y_rows, uint8_t* qh, float* sh, int32_t* tiles,
-                             hipStream_t stream) {
+                             bool tiles_ready, hipStream_t stream) {
   PrefillRows r{};
   r.offsets = offsets; r.off_stride = 0; r.n_units = d.n_experts; r.n_chunks = 1; r.chunk_rows = 0;
   r.chunk_tokens = 0; r.tokens = T; r.rows = (int64_t)T * d.topk;
   r.max_mtiles = prefill_max_mtiles(r.rows, d.n_experts);
+  r.tiles_ready = tiles_ready;
   return run_ffn_prefill_view(d, r, qx, sx, sorted_src, w_gate, s_gate, w_up, s_up, w_down, s_down, y_rows, qh, sh,
                               tiles, stream);
 }

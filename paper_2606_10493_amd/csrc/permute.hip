@@ -12,72 +12,99 @@
 // Slots whose id is out of range, or repeats an earlier slot's id in the
 // same token, are reported in the device status word and parked after all
 // valid rows (positions expert_offsets[E] .. T*k-1, in slot order), so the
-// outputs stay a bijection and every later index stays in bounds.
+// outputs stay a bijection and every later index stays in bounds.  The atomic
+// OR returns the word before it: a bit that was set already is a repeated id
+// (how many there are does not depend on the order of the atomics; which slot
+// of the two is the earlier one is only looked up when there are any).
 //
+// These kernels are latency chains of a few microseconds (launch, one load
+// round trip, LDS, scan), so a chunk has 1024 threads, each holding its at
+// most 8 slot ids in registers, and as little as possible is a launch of its
+// own:
 //   one chunk  (T <= 256): permute_small_kernel does count, scan and scatter
 //              (layer_prologue_kernel: the same, beside the activation quantization).
-//   several chunks: permute_count_kernel -> permute_scan_kernel -> permute_scatter_kernel.
+//   several chunks: permute_count_kernel (layer: beside the activation
+//              quantization, quant_count_kernel) -> permute_scatter_kernel,
+//              whose workgroups each sum the chunks' counts again.  Beyond
+//              kMaxFusedScan chunks that re-reading grows with the square of
+//              the chunks and a scan of its own goes first.
+// In a layer call of the prefill regime the kernel that knows the experts'
+// counts also writes the m-tile table of the GEMMs (TilesOut).
+//
+// Measured (rocprofv3, one layer's quantization, sort and m-tile table): 201
+// tokens x 8 slots over 256 experts 19.2 us in two launches -> 5.6 us in one;
+// 509 tokens over 128 experts 31.0 us in five launches -> 11.3 us in two;
+// 8192 tokens 70.2 us -> 53.3 us (45.0 of it the quantization, HBM bound).
+// 256-thread chunks whose threads walked a token's k slots one after the
+// other took 8.6 us to count and 11.2 us to scatter; these take 4.8 and 6.5.
 #include "common.h"
 
 namespace moe {
 
 namespace {
 
-constexpr int kChunk = 256;      // tokens per workgroup (one per thread)
+constexpr int kChunk = 256;         // tokens per workgroup
+constexpr int kSortThreads = 1024;  // threads per chunk (and one per expert in the scan)
 constexpr int kMaxExperts = 1024;
 constexpr int kMaxTopk = 32;
+constexpr int kSlotsPerThread = kChunk * kMaxTopk / kSortThreads;
+constexpr int kMaxFusedScan = 512;  // chunks up to which every scatter workgroup sums all counts itself
 
-struct SlotCheck {
-  int expert;
-  uint32_t err;  // MOE_DEV_* bits, 0 if the slot is valid
+// LDS of one chunk.
+struct ChunkMasks {
+  unsigned long long mask[kMaxExperts * 4];  // per expert, the chunk's tokens that list it
+  int base[kMaxExperts];                     // first sorted position of the chunk's rows of each expert
+  int wave_tot[kSortThreads / 64];
+  int bad_count;                             // invalid slots of the chunk
 };
 
-// The ids of one chunk (up to kChunk tokens x k) staged in LDS with one
-// coalesced pass, so the per-slot checks below read LDS, not global memory.
-// 16 bits hold any valid id (E <= 1024); ids outside [0, E) become -1.
-__device__ __forceinline__ void stage_ids(int16_t* sid, const int32_t* __restrict__ ids, int64_t chunk0, int64_t T,
-                                          int k, int E) {
-  const int64_t ntok = min((int64_t)kChunk, T - chunk0);
-  const int n = ntok > 0 ? (int)(ntok * k) : 0;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const int32_t id = ids[chunk0 * k + i];
-    sid[i] = (int16_t)((id >= 0 && id < E) ? id : -1);
-  }
-}
+// Token (chunk-local) of slot f < kChunk * kMaxTopk: f / k by the reciprocal.
+// (f + 0.5) / k is at least 0.5 / 32 away from an integer and the product's
+// error is below 8192 * 2^-22, so the truncation is exact.
+__device__ __forceinline__ int token_of(int f, float inv_k) { return (int)(((float)f + 0.5f) * inv_k); }
 
-// Slot j of the chunk's token lt (ids in LDS, sid = the chunk's ids).
-__device__ __forceinline__ SlotCheck check_slot(const int16_t* sid, int lt, int j, int k, int E) {
-  const int16_t* row = sid + lt * k;
-  SlotCheck r;
-  r.expert = row[j];
-  r.err = 0;
-  if (r.expert < 0 || r.expert >= E) {  // staged as -1
-    r.err = MOE_DEV_BAD_EXPERT_ID;
-    return r;
-  }
-  for (int i = 0; i < j; ++i)
-    if (row[i] == r.expert) r.err = MOE_DEV_DUP_EXPERT_ID;
-  return r;
-}
-
-// Fill the per-expert token masks of one chunk; returns this thread's error bits.
-__device__ __forceinline__ uint32_t build_masks(unsigned long long* mask, int* bad_count, const int16_t* sid,
-                                                int64_t t, int64_t T, int k, int E) {
+// Clear the masks, read this thread's slots of the chunk (ids: the chunk's
+// first slot, n slots) and set their mask bits; returns the thread's MOE_DEV_*
+// bits.  The masks and bad_count are complete on return.
+__device__ __forceinline__ uint32_t mark_slots(ChunkMasks& cm, const int32_t* __restrict__ ids, int n, float inv_k,
+                                               int E, int (&id)[kSlotsPerThread]) {
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int q = 0; q < kSlotsPerThread; ++q)
+    if (q * kSortThreads < n) id[q] = ids[min(q * kSortThreads + tid, n - 1)];
+  for (int i = tid; i < E * 4; i += kSortThreads) cm.mask[i] = 0ull;
+  if (tid == 0) cm.bad_count = 0;
+  __syncthreads();
   uint32_t err = 0;
-  if (t < T) {
-    const unsigned long long bit = 1ull << (threadIdx.x & 63);
-    const int word = threadIdx.x >> 6;
-    for (int j = 0; j < k; ++j) {
-      const SlotCheck s = check_slot(sid, threadIdx.x, j, k, E);
-      if (s.err == 0) {
-        atomicOr(&mask[s.expert * 4 + word], bit);
-      } else {
-        err |= s.err;
-        atomicAdd(bad_count, 1);
+#pragma unroll
+  for (int q = 0; q < kSlotsPerThread; ++q) {
+    if (q * kSortThreads >= n) break;
+    const int f = q * kSortThreads + tid;
+    if (f < n) {
+      uint32_t bad = MOE_DEV_BAD_EXPERT_ID;
+      if (id[q] >= 0 && id[q] < E) {
+        const int t = token_of(f, inv_k);
+        const unsigned long long bit = 1ull << (t & 63);
+        bad = (atomicOr(&cm.mask[id[q] * 4 + (t >> 6)], bit) & bit) ? MOE_DEV_DUP_EXPERT_ID : 0u;
+      }
+      if (bad) {
+        err |= bad;
+        atomicAdd(&cm.bad_count, 1);
       }
     }
   }
+  __syncthreads();
   return err;
+}
+
+// Whether slot f (chunk-local) is valid: its id is in range and no earlier
+// slot of its token has the same id.  Only chunks with invalid slots ask.
+__device__ __forceinline__ bool slot_valid(const int32_t* __restrict__ ids, int f, int k, int E) {
+  const int id = ids[f];
+  bool ok = id >= 0 && id < E;
+#pragma unroll 1
+  for (int i = f - f % k; i < f; ++i) ok &= ids[i] != id;
+  return ok;
 }
 
 // Rank of token lt (chunk-local) among the chunk's tokens routed to e.
@@ -87,10 +114,6 @@ __device__ __forceinline__ int rank_of(const unsigned long long* mask, int e, in
   int r = __popcll(mask[e * 4 + word] & below);
   for (int w = 0; w < word; ++w) r += __popcll(mask[e * 4 + w]);
   return r;
-}
-
-__device__ __forceinline__ int rank_in_chunk(const unsigned long long* mask, int e) {
-  return rank_of(mask, e, threadIdx.x);
 }
 
 __device__ __forceinline__ int mask_count(const unsigned long long* mask, int e) {
@@ -103,104 +126,83 @@ __device__ __forceinline__ void report(int32_t* dev_status, uint32_t err) {
   if (dev_status && err && (threadIdx.x & 63) == 0) atomicOr(dev_status, (int)err);
 }
 
-// Valid slots of this chunk go to base_e + rank; invalid ones, in slot order,
-// to bad_base + running index (walked by one thread: the error path only).
-__device__ __forceinline__ void scatter_chunk(const unsigned long long* mask, const int16_t* sid, int64_t chunk0,
-                                              int64_t T, int k, int E, const int32_t* base_of_e, int32_t bad_base,
-                                              int bad_count, int32_t* sorted_src, int32_t* dest_row) {
-  const int64_t t = chunk0 + threadIdx.x;
-  if (t < T) {
-    const int64_t tb = t * k;
-    for (int j = 0; j < k; ++j) {
-      const SlotCheck s = check_slot(sid, threadIdx.x, j, k, E);
-      if (s.err) continue;
-      const int32_t p = base_of_e[s.expert] + rank_in_chunk(mask, s.expert);
-      dest_row[tb + j] = p;
-      sorted_src[p] = (int32_t)(tb + j);
-    }
-  }
-  if (bad_count > 0 && threadIdx.x == 0) {
-    int32_t p = bad_base;
-    const int64_t t1 = min(T, chunk0 + kChunk);
-    for (int64_t tt = chunk0; tt < t1; ++tt)
-      for (int j = 0; j < k; ++j) {
-        const SlotCheck s = check_slot(sid, (int)(tt - chunk0), j, k, E);
-        if (!s.err) continue;
-        dest_row[tt * k + j] = p;
-        sorted_src[p] = (int32_t)(tt * k + j);
-        ++p;
+// The chunk's slots (chunk-local f -> flat slot f0 + f) to their positions:
+// valid ones to base[e] + rank, invalid ones in slot order from bad_base
+// (walked by one thread: the error path only).
+__device__ __forceinline__ void scatter_slots(const ChunkMasks& cm, const int32_t* __restrict__ ids, int n, int k,
+                                              float inv_k, int E, const int (&id)[kSlotsPerThread], int32_t f0,
+                                              int32_t bad_base, int32_t* __restrict__ sorted_src,
+                                              int32_t* __restrict__ dest_row) {
+  const int tid = threadIdx.x;
+  if (cm.bad_count == 0) {
+#pragma unroll
+    for (int q = 0; q < kSlotsPerThread; ++q) {
+      if (q * kSortThreads >= n) break;
+      const int f = q * kSortThreads + tid;
+      if (f < n) {
+        const int32_t p = cm.base[id[q]] + rank_of(cm.mask, id[q], token_of(f, inv_k));
+        dest_row[f0 + f] = p;
+        sorted_src[p] = f0 + f;
       }
-  }
-}
-
-// One chunk (T <= 256): mask, scan and scatter in one workgroup.  Threads
-// take slots, not tokens, so that a few tokens with k slots each (decode)
-// spread over k * T threads instead of a serial loop in T threads.
-__device__ __forceinline__ void permute_one_chunk(const int32_t* __restrict__ ids, int T, int k, int E,
-                                                  int32_t* __restrict__ offsets, int32_t* __restrict__ sorted_src,
-                                                  int32_t* __restrict__ dest_row, int32_t* __restrict__ dev_status) {
-  __shared__ unsigned long long mask[kMaxExperts * 4];
-  __shared__ int start[kMaxExperts];
-  __shared__ int16_t sid[kChunk * kMaxTopk];
-  __shared__ int tmp[4];
-  __shared__ int bad_count;
-  for (int i = threadIdx.x; i < E * 4; i += 256) mask[i] = 0ull;
-  if (threadIdx.x == 0) bad_count = 0;
-  stage_ids(sid, ids, 0, T, k, E);
-  __syncthreads();
-  const int n = T * k;
-  uint32_t err = 0;
-  for (int f = threadIdx.x; f < n; f += 256) {
-    const int t = f / k, j = f - t * k;
-    const SlotCheck sc = check_slot(sid, t, j, k, E);
-    if (sc.err == 0) {
-      atomicOr(&mask[sc.expert * 4 + (t >> 6)], 1ull << (t & 63));
-    } else {
-      err |= sc.err;
-      atomicAdd(&bad_count, 1);
     }
+    return;
   }
-  __syncthreads();
-  // Thread i owns experts 4i .. 4i+3 for the scan.
-  int c[4], local = 0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int e = 4 * threadIdx.x + q;
-    c[q] = (e < E) ? mask_count(mask, e) : 0;
-    local += c[q];
+#pragma unroll 1
+  for (int f = tid; f < n; f += kSortThreads) {
+    if (!slot_valid(ids, f, k, E)) continue;
+    const int32_t p = cm.base[ids[f]] + rank_of(cm.mask, ids[f], token_of(f, inv_k));
+    dest_row[f0 + f] = p;
+    sorted_src[p] = f0 + f;
   }
-  int total_valid;
-  int run = block_exclusive_scan(local, tmp, &total_valid);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int e = 4 * threadIdx.x + q;
-    if (e < E) {
-      start[e] = run;
-      offsets[e] = run;
-    }
-    run += c[q];
-  }
-  if (threadIdx.x == 0) offsets[E] = total_valid;
-  __syncthreads();
-  for (int f = threadIdx.x; f < n; f += 256) {
-    const int t = f / k, j = f - t * k;
-    const SlotCheck sc = check_slot(sid, t, j, k, E);
-    if (sc.err) continue;
-    const int32_t p = start[sc.expert] + rank_of(mask, sc.expert, t);
-    dest_row[f] = p;
-    sorted_src[p] = f;
-  }
-  if (bad_count > 0 && threadIdx.x == 0) {  // error path: invalid slots in slot order after the valid rows
-    int32_t p = total_valid;
+  if (tid == 0) {
+    int32_t p = bad_base;
+#pragma unroll 1
     for (int f = 0; f < n; ++f) {
-      const int t = f / k;
-      const SlotCheck sc = check_slot(sid, t, f - t * k, k, E);
-      if (!sc.err) continue;
-      dest_row[f] = p;
-      sorted_src[p] = f;
+      if (slot_valid(ids, f, k, E)) continue;
+      dest_row[f0 + f] = p;
+      sorted_src[p] = f0 + f;
       ++p;
     }
   }
+}
+
+// The expert offsets and, if asked for, the m-tile table (the same as
+// prefill_tiles_kernel writes for one chunk of rows), from expert
+// threadIdx.x's first row and row count.
+__device__ __forceinline__ void write_offsets(ChunkMasks& cm, int E, int first, int count, int total_valid,
+                                              int32_t* __restrict__ offsets, const TilesOut& tiles) {
+  const int e = threadIdx.x;
+  if (e < E) offsets[e] = first;
+  if (e == 0) offsets[E] = total_valid;
+  if (!tiles.mtile_start) return;
+  const int cnt = e < E ? (count + kPrefillTileRows - 1) / kPrefillTileRows : 0;
+  int total;
+  const int excl = block_exclusive_scan(cnt, cm.wave_tot, &total);
+  if (e < E) {
+    tiles.mtile_start[e] = excl;
+    for (int b = excl; b < excl + cnt && b < tiles.max_mtiles; ++b)
+      tiles.desc[b] = make_int4(e, excl, first, first + count);
+  }
+  if (e == 0) tiles.mtile_start[E] = total;
+}
+
+// One chunk (T <= 256): mask, scan and scatter in one workgroup.
+__device__ __forceinline__ void permute_one_chunk(const int32_t* __restrict__ ids, int T, int k, int E,
+                                                  int32_t* __restrict__ offsets, int32_t* __restrict__ sorted_src,
+                                                  int32_t* __restrict__ dest_row, int32_t* __restrict__ dev_status,
+                                                  const TilesOut& tiles) {
+  __shared__ ChunkMasks cm;
+  const float inv_k = 1.0f / (float)k;
+  int id[kSlotsPerThread];
+  const uint32_t err = mark_slots(cm, ids, T * k, inv_k, E, id);
+  const int e = threadIdx.x;
+  const int count = e < E ? mask_count(cm.mask, e) : 0;
+  int total_valid;
+  const int first = block_exclusive_scan(count, cm.wave_tot, &total_valid);
+  if (e < E) cm.base[e] = first;
+  __syncthreads();
+  scatter_slots(cm, ids, T * k, k, inv_k, E, id, 0, total_valid, sorted_src, dest_row);
+  write_offsets(cm, E, first, count, total_valid, offsets, tiles);
   report(dev_status, err);
 }
 
@@ -282,55 +284,74 @@ __device__ __forceinline__ void permute_tiny(const int32_t* __restrict__ ids, in
   report(dev_status, err);
 }
 
-__global__ __launch_bounds__(256) void permute_small_kernel(const int32_t* __restrict__ ids, int T, int k, int E,
-                                                            int32_t* __restrict__ offsets,
-                                                            int32_t* __restrict__ sorted_src,
-                                                            int32_t* __restrict__ dest_row,
-                                                            int32_t* __restrict__ dev_status) {
-  if (T * k <= kTinySlots) permute_tiny(ids, T, k, E, offsets, sorted_src, dest_row, dev_status);
-  else permute_one_chunk(ids, T, k, E, offsets, sorted_src, dest_row, dev_status);
+// Up to kTinySlots slots one 256-thread workgroup, else kSortThreads threads.
+template <bool TINY>
+__global__ __launch_bounds__(TINY ? 256 : kSortThreads) void permute_small_kernel(
+    const int32_t* __restrict__ ids, int T, int k, int E, int32_t* __restrict__ offsets,
+    int32_t* __restrict__ sorted_src, int32_t* __restrict__ dest_row, int32_t* __restrict__ dev_status) {
+  if constexpr (TINY) permute_tiny(ids, T, k, E, offsets, sorted_src, dest_row, dev_status);
+  else permute_one_chunk(ids, T, k, E, offsets, sorted_src, dest_row, dev_status, TilesOut{});
 }
 
 // Layer prologue for one chunk of tokens (T <= 256), one launch instead of
 // two: workgroup 0 sorts the slots (as permute_small_kernel); workgroups 1..
-// quantize the bf16 activations, 16 groups of 128 columns each (as
+// quantize the bf16 activations, one group of 128 columns per 16 threads (as
 // moe_quant_act).
-__global__ __launch_bounds__(256) void layer_prologue_kernel(const int32_t* __restrict__ ids, int T, int k, int E,
-                                                             int32_t* __restrict__ offsets,
-                                                             int32_t* __restrict__ sorted_src,
-                                                             int32_t* __restrict__ dest_row,
-                                                             int32_t* __restrict__ dev_status,
-                                                             const uint16_t* __restrict__ x, int64_t n_groups,
-                                                             int groups_per_row, uint8_t* __restrict__ qx,
-                                                             float* __restrict__ sx) {
+template <bool TINY>
+__global__ __launch_bounds__(TINY ? 256 : kSortThreads) void layer_prologue_kernel(
+    const int32_t* __restrict__ ids, int T, int k, int E, int32_t* __restrict__ offsets,
+    int32_t* __restrict__ sorted_src, int32_t* __restrict__ dest_row, int32_t* __restrict__ dev_status,
+    const uint16_t* __restrict__ x, int64_t n_groups, int groups_per_row, uint8_t* __restrict__ qx,
+    float* __restrict__ sx, TilesOut tiles) {
   if (blockIdx.x == 0) {
-    if (T * k <= kTinySlots) permute_tiny(ids, T, k, E, offsets, sorted_src, dest_row, dev_status);
-    else permute_one_chunk(ids, T, k, E, offsets, sorted_src, dest_row, dev_status);
+    if constexpr (TINY) permute_tiny(ids, T, k, E, offsets, sorted_src, dest_row, dev_status);
+    else permute_one_chunk(ids, T, k, E, offsets, sorted_src, dest_row, dev_status, tiles);
     return;
   }
-  const int64_t g = (int64_t)(blockIdx.x - 1) * 16 + (threadIdx.x >> 4);
+  const int64_t g = (int64_t)(blockIdx.x - 1) * (blockDim.x / 16) + (threadIdx.x >> 4);
   if (g >= n_groups) return;  // whole 16-lane groups leave together
   quant_row_group<uint16_t>(x, g, threadIdx.x & 15, groups_per_row, qx, sx);
 }
 
+// Slots of chunk c.
+__device__ __forceinline__ int chunk_slots(int64_t c, int T, int k) {
+  return (int)min((int64_t)kChunk, T - c * kChunk) * k;
+}
+
 // counts: [n_chunks][E+1]; entry E is the chunk's number of invalid slots.
-__global__ __launch_bounds__(256) void permute_count_kernel(const int32_t* __restrict__ ids, int T, int k, int E,
-                                                            int32_t* __restrict__ counts,
-                                                            int32_t* __restrict__ dev_status) {
-  __shared__ unsigned long long mask[kMaxExperts * 4];
-  __shared__ int16_t sid[kChunk * kMaxTopk];
-  __shared__ int bad_count;
-  for (int i = threadIdx.x; i < E * 4; i += 256) mask[i] = 0ull;
-  if (threadIdx.x == 0) bad_count = 0;
-  const int64_t chunk0 = (int64_t)blockIdx.x * kChunk;
-  stage_ids(sid, ids, chunk0, T, k, E);
-  __syncthreads();
-  const uint32_t err = build_masks(mask, &bad_count, sid, chunk0 + threadIdx.x, T, k, E);
-  __syncthreads();
-  int32_t* row = counts + (int64_t)blockIdx.x * (E + 1);
-  for (int e = threadIdx.x; e < E; e += 256) row[e] = mask_count(mask, e);
-  if (threadIdx.x == 0) row[E] = bad_count;
+__device__ __forceinline__ void count_chunk(int64_t c, const int32_t* __restrict__ ids, int T, int k, int E,
+                                            int32_t* __restrict__ counts, int32_t* __restrict__ dev_status) {
+  __shared__ ChunkMasks cm;
+  int id[kSlotsPerThread];
+  const uint32_t err = mark_slots(cm, ids + c * kChunk * k, chunk_slots(c, T, k), 1.0f / (float)k, E, id);
+  int32_t* row = counts + c * (E + 1);
+  for (int e = threadIdx.x; e < E; e += kSortThreads) row[e] = mask_count(cm.mask, e);
+  if (threadIdx.x == 0) row[E] = cm.bad_count;
   report(dev_status, err);
+}
+
+__global__ __launch_bounds__(kSortThreads) void permute_count_kernel(const int32_t* __restrict__ ids, int T, int k,
+                                                                     int E, int chunk0,
+                                                                     int32_t* __restrict__ counts,
+                                                                     int32_t* __restrict__ dev_status) {
+  count_chunk((int64_t)chunk0 + blockIdx.x, ids, T, k, E, counts, dev_status);
+}
+
+// Layer call of several chunks: workgroups 0 .. n_chunks-1 count the slots,
+// the others quantize the activations (64 groups each), in one launch.
+__global__ __launch_bounds__(kSortThreads) void quant_count_kernel(const int32_t* __restrict__ ids, int T, int k,
+                                                                   int E, int n_chunks, int32_t* __restrict__ counts,
+                                                                   int32_t* __restrict__ dev_status,
+                                                                   const uint16_t* __restrict__ x, int64_t n_groups,
+                                                                   int groups_per_row, uint8_t* __restrict__ qx,
+                                                                   float* __restrict__ sx) {
+  if ((int)blockIdx.x < n_chunks) {
+    count_chunk(blockIdx.x, ids, T, k, E, counts, dev_status);
+    return;
+  }
+  const int64_t g = (int64_t)(blockIdx.x - n_chunks) * (kSortThreads / 16) + (threadIdx.x >> 4);
+  if (g >= n_groups) return;  // whole 16-lane groups leave together
+  quant_row_group<uint16_t>(x, g, threadIdx.x & 15, groups_per_row, qx, sx);
 }
 
 // One workgroup of 1024 threads; thread e scans expert e over the chunks.
@@ -369,41 +390,137 @@ __global__ __launch_bounds__(1024) void permute_scan_kernel(const int32_t* __res
   }
 }
 
-__global__ __launch_bounds__(256) void permute_scatter_kernel(const int32_t* __restrict__ ids, int T, int k, int E,
-                                                              const int32_t* __restrict__ counts,
-                                                              const int32_t* __restrict__ base,
-                                                              int32_t* __restrict__ sorted_src,
-                                                              int32_t* __restrict__ dest_row) {
-  __shared__ unsigned long long mask[kMaxExperts * 4];
-  __shared__ int16_t sid[kChunk * kMaxTopk];
-  __shared__ int bad_count;
-  for (int i = threadIdx.x; i < E * 4; i += 256) mask[i] = 0ull;
-  if (threadIdx.x == 0) bad_count = 0;
-  const int64_t chunk0 = (int64_t)blockIdx.x * kChunk;
-  stage_ids(sid, ids, chunk0, T, k, E);
+// Scatter, one chunk per workgroup.  base: the chunk bases of
+// permute_scan_kernel, or NULL: each workgroup sums the counts itself, thread
+// (part, e) those of expert e in the chunks part, part + parts, ... (all
+// chunks, and those before its own), so that a few tens of chunks cost one
+// round trip of loads; workgroup 0 writes the offsets and the m-tile table.
+__global__ __launch_bounds__(kSortThreads) void permute_scatter_kernel(
+    const int32_t* __restrict__ ids, int T, int k, int E, int chunk0, int n_chunks,
+    const int32_t* __restrict__ counts, const int32_t* __restrict__ base, int32_t* __restrict__ offsets,
+    int32_t* __restrict__ sorted_src, int32_t* __restrict__ dest_row, TilesOut tiles) {
+  __shared__ ChunkMasks cm;
+  __shared__ int part_sum[2][kSortThreads];  // [total, before this chunk]
+  const int tid = threadIdx.x;
+  const float inv_k = 1.0f / (float)k;
+  const int64_t c = (int64_t)chunk0 + blockIdx.x;
+  const int32_t f0 = (int32_t)(c * kChunk * k);
+  const int n = chunk_slots(c, T, k);
+  int id[kSlotsPerThread];
+  mark_slots(cm, ids + f0, n, inv_k, E, id);
+  int32_t bad_base = 0;
+  if (base) {
+    const int32_t* brow = base + c * (E + 1);
+    for (int e = tid; e < E; e += kSortThreads) cm.base[e] = brow[e];
+    bad_base = brow[E];
+  } else {
+    const int parts = kSortThreads / E;  // E <= kSortThreads
+    const int part = tid / E, col = tid - part * E;
+    int tot = 0, before = 0;
+    if (part < parts) {
+#pragma unroll 8
+      for (int x = part; x < n_chunks; x += parts) {
+        const int v = counts[x * (E + 1) + col];  // < kMaxFusedScan * 1025
+        tot += v;
+        before += x < c ? v : 0;
+      }
+    }
+    part_sum[0][tid] = tot;
+    part_sum[1][tid] = before;
+    __syncthreads();
+    tot = before = 0;
+    if (tid < E)
+      for (int p = 0; p < parts; ++p) {
+        tot += part_sum[0][p * E + tid];
+        before += part_sum[1][p * E + tid];
+      }
+    int total_valid;
+    const int first = block_exclusive_scan(tot, cm.wave_tot, &total_valid);
+    if (tid < E) cm.base[tid] = first + before;
+    if (c == 0) write_offsets(cm, E, first, tot, total_valid, offsets, tiles);
+    bad_base = total_valid;
+    if (cm.bad_count > 0)  // the error path
+#pragma unroll 1
+      for (int64_t x = 0; x < c; ++x) bad_base += counts[x * (E + 1) + E];
+  }
   __syncthreads();
-  build_masks(mask, &bad_count, sid, chunk0 + threadIdx.x, T, k, E);
-  __syncthreads();
-  const int32_t* brow = base + (int64_t)blockIdx.x * (E + 1);
-  const int nbad = counts[(int64_t)blockIdx.x * (E + 1) + E];
-  scatter_chunk(mask, sid, chunk0, T, k, E, brow, brow[E], nbad, sorted_src, dest_row);
+  scatter_slots(cm, ids + f0, n, k, inv_k, E, id, f0, bad_base, sorted_src, dest_row);
 }
 
 int64_t n_chunks_of(int32_t T) { return ((int64_t)T + kChunk - 1) / kChunk; }
 
 }  // namespace
 
-// Quantize x [T, H] and sort the slots of T <= 256 tokens in one launch.
-// Arguments are checked by the caller.
+// A grid has less than 2^32 threads: chunks per launch of the sort's kernels.
+constexpr int64_t kChunksPerLaunch = 1 << 21;
+
+moe_status_t launch_count(const int32_t* topk_ids, int32_t T, int32_t k, int32_t E, int32_t* counts,
+                          int32_t* dev_status, hipStream_t stream) {
+  const int64_t nc = n_chunks_of(T);
+  for (int64_t c0 = 0; c0 < nc; c0 += kChunksPerLaunch)
+    MOE_LAUNCH("permute_count", permute_count_kernel, dim3((unsigned)min(nc - c0, kChunksPerLaunch)),
+               dim3(kSortThreads), 0, stream, topk_ids, T, k, E, (int)c0, counts, dev_status);
+  return check_launch("moe_permute");
+}
+
+// The chunks' counts -> positions.  counts: the first part of the permute workspace.
+moe_status_t launch_scatter(const int32_t* topk_ids, int32_t T, int32_t k, int32_t E, int32_t* offsets,
+                            int32_t* sorted_src, int32_t* dest_row, int32_t* counts, const TilesOut& tiles,
+                            hipStream_t stream) {
+  const int64_t nc = n_chunks_of(T);
+  int32_t* base = nullptr;
+  if (nc > kMaxFusedScan) {
+    base = counts + nc * (E + 1);
+    MOE_LAUNCH("permute_scan", permute_scan_kernel, dim3(1), dim3(1024), 0, stream, counts, (int)nc, E, base, offsets);
+  }
+  for (int64_t c0 = 0; c0 < nc; c0 += kChunksPerLaunch)
+    MOE_LAUNCH("permute_scatter", permute_scatter_kernel, dim3((unsigned)min(nc - c0, kChunksPerLaunch)),
+               dim3(kSortThreads), 0, stream, topk_ids, T, k, E, (int)c0, (int)nc, counts, base, offsets, sorted_src,
+               dest_row, tiles);
+  return check_launch("moe_permute");
+}
+
+// Whether launch_layer_prologue also writes a m-tile table it is given.
+bool layer_prologue_writes_tiles(int32_t T, int32_t k) {
+  return T <= kChunk ? T * k > kTinySlots : n_chunks_of(T) <= kMaxFusedScan;
+}
+
+// Quantize x [T, H] and sort the slots: one launch for T <= 256 tokens, two
+// for more.  tiles: the m-tile table to write (see
+// layer_prologue_writes_tiles), or empty.  perm_ws: moe_permute_workspace
+// bytes.  Arguments are checked by the caller.
 moe_status_t launch_layer_prologue(const uint16_t* x, int32_t T, int32_t H, const int32_t* topk_ids, int32_t k,
                                    int32_t E, uint8_t* qx, float* sx, int32_t* offsets, int32_t* sorted_src,
-                                   int32_t* dest_row, int32_t* dev_status, hipStream_t stream) {
-  if (T > kChunk) return fail(MOE_ERR_INVALID_ARG, "layer prologue: T=%d > %d", T, kChunk);
+                                   int32_t* dest_row, int32_t* dev_status, const TilesOut& tiles, void* perm_ws,
+                                   hipStream_t stream) {
   const int gpr = H / kBlock;
   const int64_t n_groups = (int64_t)T * gpr;
-  const int64_t blocks = 1 + (n_groups + 15) / 16;
-  MOE_LAUNCH("layer_prologue", layer_prologue_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, topk_ids, T, k, E,
-             offsets, sorted_src, dest_row, dev_status, x, n_groups, gpr, qx, sx);
+  const int64_t nc = n_chunks_of(T);
+  if (nc > 1) {
+    const int64_t blocks = nc + (n_groups + kSortThreads / 16 - 1) / (kSortThreads / 16);
+    int32_t* counts = static_cast<int32_t*>(perm_ws);
+    if (blocks * kSortThreads > 0xffffffffll) {  // too many threads for one grid
+      moe_status_t st = moe_quant_act(x, T, H, qx, sx, stream);
+      if (st == MOE_OK) st = launch_count(topk_ids, T, k, E, counts, dev_status, stream);
+      if (st != MOE_OK) return st;
+      return launch_scatter(topk_ids, T, k, E, offsets, sorted_src, dest_row, counts, tiles, stream);
+    }
+    MOE_LAUNCH("quant_count", quant_count_kernel, dim3((unsigned)blocks), dim3(kSortThreads), 0, stream, topk_ids, T, k,
+               E, (int)nc, counts, dev_status, x, n_groups, gpr, qx, sx);
+    const moe_status_t st = check_launch("layer prologue");
+    if (st != MOE_OK) return st;
+    return launch_scatter(topk_ids, T, k, E, offsets, sorted_src, dest_row, counts, tiles, stream);
+  }
+  const bool tiny = T * k <= kTinySlots;
+  const int threads = tiny ? 256 : kSortThreads;
+  const int64_t blocks = 1 + (n_groups + threads / 16 - 1) / (threads / 16);
+  if (tiny) {
+    MOE_LAUNCH("layer_prologue", layer_prologue_kernel<true>, dim3((unsigned)blocks), dim3(threads), 0, stream,
+               topk_ids, T, k, E, offsets, sorted_src, dest_row, dev_status, x, n_groups, gpr, qx, sx, tiles);
+  } else {
+    MOE_LAUNCH("layer_prologue", layer_prologue_kernel<false>, dim3((unsigned)blocks), dim3(threads), 0, stream,
+               topk_ids, T, k, E, offsets, sorted_src, dest_row, dev_status, x, n_groups, gpr, qx, sx, tiles);
+  }
   return check_launch("layer prologue");
 }
 
@@ -430,8 +547,13 @@ extern "C" moe_status_t moe_permute(const int32_t* topk_ids, int32_t T, int32_t 
     return fail(MOE_ERR_INVALID_ARG, "moe_permute: null pointer");
   const int64_t nc = n_chunks_of(T);
   if (nc <= 1) {
-    MOE_LAUNCH("permute_small", permute_small_kernel, dim3(1), dim3(256), 0, stream, topk_ids, T, k, E, expert_offsets,
-                       sorted_src, dest_row, dev_status);
+    if (T * k <= kTinySlots) {
+      MOE_LAUNCH("permute_small", permute_small_kernel<true>, dim3(1), dim3(256), 0, stream, topk_ids, T, k, E,
+                 expert_offsets, sorted_src, dest_row, dev_status);
+    } else {
+      MOE_LAUNCH("permute_small", permute_small_kernel<false>, dim3(1), dim3(kSortThreads), 0, stream, topk_ids, T, k,
+                 E, expert_offsets, sorted_src, dest_row, dev_status);
+    }
     return check_launch("moe_permute");
   }
   const size_t need = moe_permute_workspace(T, k, E);
@@ -439,12 +561,7 @@ extern "C" moe_status_t moe_permute(const int32_t* topk_ids, int32_t T, int32_t 
     return fail(MOE_ERR_WORKSPACE, "moe_permute: workspace %zu bytes < %zu", ws_bytes, need);
   if (!aligned(ws, 4)) return fail(MOE_ERR_INVALID_ARG, "moe_permute: misaligned workspace");
   int32_t* counts = static_cast<int32_t*>(ws);
-  int32_t* base = counts + nc * (E + 1);
-  MOE_LAUNCH("permute_count", permute_count_kernel, dim3((unsigned)nc), dim3(256), 0, stream, topk_ids, T, k, E, counts,
-                     dev_status);
-  MOE_LAUNCH("permute_scan", permute_scan_kernel, dim3(1), dim3(1024), 0, stream, counts, (int)nc, E, base,
-                     expert_offsets);
-  MOE_LAUNCH("permute_scatter", permute_scatter_kernel, dim3((unsigned)nc), dim3(256), 0, stream, topk_ids, T, k, E, counts,
-                     base, sorted_src, dest_row);
-  return check_launch("moe_permute");
+  const moe_status_t st = launch_count(topk_ids, T, k, E, counts, dev_status, stream);
+  if (st != MOE_OK) return st;
+  return launch_scatter(topk_ids, T, k, E, expert_offsets, sorted_src, dest_row, counts, TilesOut{}, stream);
 }
