@@ -266,6 +266,27 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* wave_tot, int* t
   return pre + x - v;
 }
 
+// Asynchronous global -> LDS copies.  One call moves 1 KB: lane l's 16 bytes
+// at src go to LDS byte lds + 16 l (lds: the wave's LDS byte address, uniform),
+// with no registers in between.  The compiler does not track them (its own
+// builtin makes every later LDS read wait for all of them): a reader waits
+// with wait_async_and_barrier.  They count in vmcnt and complete in order.
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
+__device__ __forceinline__ void async_load_1k(const void* src, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+               :
+               : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(src)
+               : "memory");
+}
+// Waits until at most N of this wave's newest loads and stores are
+// outstanding and its LDS operations are done, then the workgroup barrier.
+template <int N>
+__device__ __forceinline__ void wait_async_and_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
+}
+
 // ----------------------------------------------------------------- host side
 void prof_before(hipStream_t s, const char* name);
 void prof_after(hipStream_t s);

@@ -77,127 +77,147 @@ __global__ __launch_bounds__(256) void router_logits_kernel(const uint16_t* __re
     }
 }
 
-// Many tokens: an LDS-tiled bf16 GEMM.  Workgroup = TM tokens x 256
-// experts over one K slice, 512 threads; wave w computes tokens
-// TM/2 (w / 4) + [0, TM/2) against experts 64 (w % 4) + [0, 64) (TM/8 MFMA
-// 16x16x32 per 32-K step).  The 32-K tiles of both operands go through two
-// LDS stages (each thread loads TM/8 bytes of x and 32 bytes of W_r per
-// step); a 64-byte LDS row holds one row's 32 K values, which a quarter wave
-// reads as 16 rows x 64 contiguous bytes.  The global loads run RING - 1
-// steps ahead through a ring of registers (four slots for 128-token tiles,
-// three for 256, which need twice the registers per slot): with one step of
-// look-ahead the
-// kernel was bound by the loads' latency (224.8 us at 32768 tokens, against
-// 161.7 us with the ring).  Every tile reads the whole router weight (3.67 MB
-// at the DeepSeek-V3 shape) from L2, so from 32768 tokens on, where 128-token
-// tiles alone fill the chip, tiles of 256 tokens halve those reads (143.8
-// against 161.7 us); below, the K slices that 256-token tiles need to fill
-// the chip cost more than they save (8192 tokens: 43.8 against 43.0 us, and
-// a slower selection over twice the slices).
-constexpr int kRtN = 256, kRtK = 32;
-constexpr int kRtBigTokens = 32768;  // 256-token tiles from here on
-inline int router_tile_tokens(int64_t T) { return T >= kRtBigTokens ? 256 : 128; }
+// Many tokens: an LDS-tiled bf16 GEMM.  Workgroup = 128 tokens x 256 experts
+// over one K slice, 512 threads; wave w computes tokens 64 (w / 4) + [0, 64)
+// against experts 64 (w % 4) + [0, 64), 16 MFMA 16x16x32 per 32 K.  64-K tiles
+// of both operands go from global memory straight into three LDS stages
+// (async_load_1k), two steps ahead, with one barrier per step.
+//
+// What bounds it is the loads' address path, and that depends on how many
+// bytes of a row a load takes together: from L2, 1 KB loads of sixteen 64-byte
+// row pieces reach 76 GB/s per CU, of eight 128-byte pieces 124 GB/s.  With
+// 32-K tiles (64-byte pieces) neither deeper look-ahead, nor operands always
+// in cache, nor leaving the MFMAs out changed the time by more than a tenth
+// (8192 tokens: 43 - 50 us).  A 128-byte LDS row holds one row's 64 K values,
+// its 16-byte chunk c at position c ^ (row / 2) % 8, so a quarter wave's reads
+// fill all 64 banks (229 B/clk; c ^ row / 4 of a 64-byte row: 120).
+// The K slice is the fastest grid index: workgroups are dealt to the eight
+// XCDs in turn, so with 2, 4 or 8 slices an XCD's L2 holds one slice of W_r.
+// Loading x further ahead than W_r (separate waves, 4 + 3 and 5 + 2 stages) did
+// not help: 41 and 53 us at 8192 tokens.
+// Measured (rocprofv3, H 7168, E 256; before: 32-K tiles through a register
+// ring, 256-token tiles from 32768 tokens): 1500 tokens 16.3 -> 14.6 us, 8192
+// tokens 47.0 -> 39.3 us, 16384 tokens 90.7 -> 69.5 us, 32768 tokens 150 ->
+// 130 us (and one K slice instead of two, so half the partial logits).
+constexpr int kRtM = 128, kRtN = 256, kRtK = 64, kRtRow = 2 * kRtK;
+constexpr int kRtStages = 3;
 
-template <int TM, int RING>
 __global__ __launch_bounds__(512) void router_logits_tiled_kernel(const uint16_t* __restrict__ x, int T, int H,
                                                                   const uint16_t* __restrict__ w, int E, int kchunk,
                                                                   float* __restrict__ part) {
-  constexpr int XR = TM / 128;  // x rows per loader thread
-  constexpr int WI = TM / 32;   // 16-token MFMA tiles per wave
-  __shared__ __attribute__((aligned(16))) uint16_t xs[2][TM * kRtK];
-  __shared__ __attribute__((aligned(16))) uint16_t wsm[2][kRtN * kRtK];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int kStage = (kRtM + kRtN) * kRtRow;
+  constexpr int kLoads = kStage / 1024 / 8;  // per wave and step, each 8 rows of 128 bytes
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[kRtStages * kStage];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, kq = lane >> 4;
   const int wm = wave >> 2, wn = wave & 3;
-  const int t0 = blockIdx.x * TM, e0 = blockIdx.y * kRtN, ks = blockIdx.z;
+  const int ks = blockIdx.x, t0 = blockIdx.y * kRtM, e0 = blockIdx.z * kRtN;
   const int64_t k0 = (int64_t)ks * kchunk;
-  // Loader: thread tid moves x rows tid / 4 (+ 128) and W_r rows tid / 4 and
-  // 128 + tid / 4 (16 bytes each at K 8 (tid % 4)); rows beyond T or E read
-  // a valid row.
-  const int lr = tid >> 2, lk = (tid & 3) * 8;
-  const uint16_t* xg0 = x + (int64_t)min(t0 + lr, T - 1) * H + k0 + lk;
-  const uint16_t* xg1 = x + (int64_t)min(t0 + (XR - 1) * 128 + lr, T - 1) * H + k0 + lk;
-  const uint16_t* wg0 = w + (int64_t)min(e0 + lr, E - 1) * H + k0 + lk;
-  const uint16_t* wg1 = w + (int64_t)min(e0 + 128 + lr, E - 1) * H + k0 + lk;
-  v4f acc[WI][4];
+  // Loader: load i of wave w takes stage rows 64 i + 8 w + [0, 8) (x rows 0 -
+  // 127, then W_r rows; rows beyond T or E read a valid row), lane l the 16
+  // bytes at LDS position l % 8 of row l / 8.
+  const int lrow = 8 * wave + (lane >> 3), lk = ((lane & 7) ^ ((lrow >> 1) & 7)) * 8;
+  const uint16_t* src[kLoads];
 #pragma unroll
-  for (int i = 0; i < WI; ++i)
+  for (int i = 0; i < kLoads; ++i) {
+    const int row = 64 * i + lrow;
+    src[i] = (i < kRtM / 64 ? x + (int64_t)min(t0 + row, T - 1) * H : w + (int64_t)min(e0 + row - kRtM, E - 1) * H) + k0;
+  }
+  const uint32_t lds0 = lds_address(smem) + wave * 1024;
+  const int nsteps = (kchunk + kRtK - 1) / kRtK;
+  // Steps past the end load the last one again, so every step issues the same
+  // loads and the wait count is a constant; a last step of 32 K reads valid
+  // values in place of its second half, which is not multiplied.
+  int ahead = 0, fill = 0;  // the step being loaded, and its stage
+  auto load_part = [&](int i) {
+    const int k = min(min(ahead, nsteps - 1) * kRtK + lk, kchunk - 8);
+    async_load_1k(src[i] + k, lds0 + fill * kStage + i * 8192);
+  };
+  auto load_done = [&]() {
+    ++ahead;
+    fill = fill + 1 == kRtStages ? 0 : fill + 1;
+  };
+  v4f acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-  const int nsteps = kchunk / kRtK;
-  // Ring slot S holds step st's operands for st % kRtRing == S (steps past
-  // the end reload the last one, so every step issues the same loads).
-  uint4 rxa0, rxa1, rxa2, rxa3, rxb0, rxb1, rxb2, rxb3, rwa0, rwa1, rwa2, rwa3, rwb0, rwb1, rwb2, rwb3;
-#define MOE_RT_LOAD(S, ST)                                                      \
-  do {                                                                          \
-    const int64_t o_ = (int64_t)min((ST), nsteps - 1) * kRtK;                   \
-    rxa##S = *reinterpret_cast<const uint4*>(xg0 + o_);                         \
-    if (XR > 1) rxb##S = *reinterpret_cast<const uint4*>(xg1 + o_);             \
-    rwa##S = *reinterpret_cast<const uint4*>(wg0 + o_);                         \
-    rwb##S = *reinterpret_cast<const uint4*>(wg1 + o_);                         \
-  } while (0)
-  // Step st in slot S: its operands into LDS stage st % 2, the barrier, the
-  // loads of step st + RING - 1 into slot NEXT (stored one step ago), then
-  // the step's MFMAs.  A stage is rewritten two steps after it was read,
-  // behind the barrier of the step in between.
-#define MOE_RT_STEP(S, NEXT, ST)                                                \
-  do {                                                                          \
-    const int st_ = (ST), b_ = st_ & 1;                                         \
-    *reinterpret_cast<uint4*>(&xs[b_][lr * kRtK + lk]) = rxa##S;                \
-    if (XR > 1) *reinterpret_cast<uint4*>(&xs[b_][(128 + lr) * kRtK + lk]) = rxb##S; \
-    *reinterpret_cast<uint4*>(&wsm[b_][lr * kRtK + lk]) = rwa##S;               \
-    *reinterpret_cast<uint4*>(&wsm[b_][(128 + lr) * kRtK + lk]) = rwb##S;       \
-    __syncthreads();                                                            \
-    MOE_RT_LOAD(NEXT, st_ + RING - 1);                                          \
-    mma_stage(b_);                                                              \
-  } while (0)
-  auto mma_stage = [&](int b) {
-    bf16x8 bb[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      bb[j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&wsm[b][(64 * wn + 16 * j + r) * kRtK + 8 * kq]));
+  for (int s = 0; s < kRtStages - 1; ++s) {
 #pragma unroll
-    for (int i = 0; i < WI; ++i) {
-      const bf16x8 a = __builtin_bit_cast(
-          bf16x8, *reinterpret_cast<const uint4*>(&xs[b][(TM / 2 * wm + 16 * i + r) * kRtK + 8 * kq]));
+    for (int i = 0; i < kLoads; ++i) load_part(i);
+    load_done();
+  }
+  // Step st's operands are read into registers while step st - 1 multiplies:
+  // the wait, the reads, the loads and the MFMAs of consecutive steps overlap.
+  // (With the reads in front of their own MFMAs, eight waves in step by the
+  // barrier spent the two one after the other.)
+  bf16x8 a[2][2][4], b[2][2][4];  // [step parity][32-K half][16-row tile]
+  int stage = 0;
+  auto fetch = [&](int buf, int h, int n) {  // tiles n of both operands
+    const int c = ((4 * h + kq) ^ (r >> 1)) << 4;  // rows 16 apart share the position
+    const uint8_t* st_ = smem + stage * kStage + r * kRtRow + c;
+    b[buf][h][n] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(st_ + (kRtM + 64 * wn + 16 * n) * kRtRow));
+    a[buf][h][n] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(st_ + (64 * wm + 16 * n) * kRtRow));
+  };
+  // Multiplies buffer 1 - buf (skipped by the first step) and meanwhile reads
+  // the next step into buffer buf.  Its loads have landed for every wave, and
+  // every wave has read the step before it, whose stage is loaded next.
+  auto step = [&](int buf, bool multiply, bool both) {
+    wait_async_and_barrier<(kRtStages - 2) * kLoads>();
+    const int m = 1 - buf;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bb[j], acc[i][j], 0, 0, 0);
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        fetch(buf, h, i);
+        if (multiply && (h == 0 || both)) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m][h][i], b[m][h][j], acc[i][j], 0, 0, 0);
+        }
+        if (4 * h + i < kLoads) load_part(4 * h + i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    load_done();
+    stage = stage + 1 == kRtStages ? 0 : stage + 1;
+  };
+  auto last = [&](int m) {
+    const bool both = nsteps * kRtK <= kchunk;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (h == 1 && !both) break;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m][h][i], b[m][h][j], acc[i][j], 0, 0, 0);
     }
   };
-  static_assert(RING == 3 || RING == 4, "the unrolled rings below have three or four slots");
-  MOE_RT_LOAD(0, 0);
-  MOE_RT_LOAD(1, 1);
-  int st = 0;
-  if constexpr (RING == 4) {
-    MOE_RT_LOAD(2, 2);
-    for (; st + 4 <= nsteps; st += 4) {
-      MOE_RT_STEP(0, 3, st);
-      MOE_RT_STEP(1, 0, st + 1);
-      MOE_RT_STEP(2, 1, st + 2);
-      MOE_RT_STEP(3, 2, st + 3);
-    }
-    if (st < nsteps) MOE_RT_STEP(0, 3, st);
-    if (st + 1 < nsteps) MOE_RT_STEP(1, 0, st + 1);
-    if (st + 2 < nsteps) MOE_RT_STEP(2, 1, st + 2);
-  } else {
-    for (; st + 3 <= nsteps; st += 3) {
-      MOE_RT_STEP(0, 2, st);
-      MOE_RT_STEP(1, 0, st + 1);
-      MOE_RT_STEP(2, 1, st + 2);
-    }
-    if (st < nsteps) MOE_RT_STEP(0, 2, st);
-    if (st + 1 < nsteps) MOE_RT_STEP(1, 0, st + 1);
+  static_assert(kLoads <= 8, "a load follows each row of MFMAs");
+  step(0, false, true);
+  int st = 1;
+  for (; st + 2 <= nsteps; st += 2) {
+    step(1, true, true);
+    step(0, true, true);
   }
-#undef MOE_RT_STEP
-#undef MOE_RT_LOAD
-  // Lane l holds logits of tokens (TM/2 wm + 16 i) + 4 kq + q for expert (64 wn + 16 j) + r.
+  if (st < nsteps) {
+    step(1, true, true);
+    last(1);
+  } else {
+    last(0);
+  }
+  // No load may reach LDS after the workgroup has ended.
+  wait_async_and_barrier<0>();
+  // Lane l holds logits of tokens (64 wm + 16 i) + 4 kq + q for expert (64 wn + 16 j) + r.
 #pragma unroll
-  for (int i = 0; i < WI; ++i)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int t = t0 + TM / 2 * wm + 16 * i + 4 * kq + q, e = e0 + 64 * wn + 16 * j + r;
+        const int t = t0 + 64 * wm + 16 * i + 4 * kq + q, e = e0 + 64 * wn + 16 * j + r;
         if (t < T && e < E) part[((int64_t)ks * T + t) * E + e] = acc[i][j][q];
       }
 }
@@ -224,32 +244,19 @@ __device__ __forceinline__ int dpp_i(int v) {
 // result over the row's 16 lanes.
 constexpr int kDppQuadXor1 = 0xB1, kDppQuadXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
 
-// Every lane gets the wave's largest (key, index) in the selection order.
-__device__ __forceinline__ void wave_argmax(float& bk, int& be) {
-  auto step = [&](float ok, int oe) {
-    if (beats(ok, oe, bk, be)) {
-      bk = ok;
-      be = oe;
-    }
-  };
-  step(dpp_f<kDppQuadXor1>(bk), dpp_i<kDppQuadXor1>(be));
-  step(dpp_f<kDppQuadXor2>(bk), dpp_i<kDppQuadXor2>(be));
-  step(dpp_f<kDppHalfMirror>(bk), dpp_i<kDppHalfMirror>(be));
-  step(dpp_f<kDppMirror>(bk), dpp_i<kDppMirror>(be));
-  // the four rows' results, as wave-uniform values
-  float k0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, bk), 0));
-  int e0 = __builtin_amdgcn_readlane(be, 0);
-#pragma unroll
-  for (int r = 1; r < 4; ++r) {
-    const float kr = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, bk), 16 * r));
-    const int er = __builtin_amdgcn_readlane(be, 16 * r);
-    if (beats(kr, er, k0, e0)) {
-      k0 = kr;
-      e0 = er;
-    }
-  }
-  bk = k0;
-  be = e0;
+constexpr int kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143;  // a row's last lane to the next row, row 1's to rows 2, 3
+
+// The wave's largest value, as a wave-uniform value: inside rows by the
+// patterns above, then across rows into lane 63.
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  auto step = [&](int o) { v = max(v, (uint32_t)o); };
+  step(dpp_i<kDppQuadXor1>((int)v));
+  step(dpp_i<kDppQuadXor2>((int)v));
+  step(dpp_i<kDppHalfMirror>((int)v));
+  step(dpp_i<kDppMirror>((int)v));
+  step(dpp_i<kDppRowBcast15>((int)v));
+  step(dpp_i<kDppRowBcast31>((int)v));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
 // Selection: one wave per token (four tokens per 256-thread workgroup),
@@ -258,10 +265,14 @@ __device__ __forceinline__ void wave_argmax(float& bk, int& be) {
 //   * group scores: for each group the two largest keys, by a wave
 //     reduction of (largest, second) pairs; lane g ranks group g against
 //     the others and the topk_group best are kept;
-//   * k <= 16: k rounds of a wave argmax over (key, index), each taking the
-//     largest remaining key, which gives the experts in slot order (k = 8:
-//     8 rounds of 6 shuffle steps against 32 dependent radix steps plus an
-//     ordering pass);
+//   * k <= 16: k rounds over the keys mapped to ordered integers, each taking
+//     the wave's largest remaining key (six max steps with lane-pattern
+//     operands) and the lowest expert that has it (PER ballots), which gives
+//     the experts in slot order.  With thousands of tokens every SIMD runs
+//     eight of these waves and the kernel is bound by their instructions, so
+//     a round is kept to about 25 of them; carrying (key, index) pairs
+//     through the reduction took about 80 (8192 tokens, E 256, k 8: 20.9 ->
+//     16.2 us; 1 token: 7.1 -> 6.0 us);
 //   * larger k: the k-th largest kept key (in the (value, index) order) by a
 //     radix select over the 32 bits of the keys mapped to ordered integers:
 //     each bit costs PER ballots, with no per-expert comparisons against all
@@ -342,6 +353,9 @@ __global__ __launch_bounds__(256) void router_select_kernel(const float* __restr
   }
 
   // Groups: score = sum of the two largest keys; lane g keeps group g's.
+  bool kept[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) kept[i] = true;
   if (n_group > 1) {
     float my_group = -INFINITY;
     if (epg <= 64 && 64 % epg == 0) {
@@ -411,50 +425,46 @@ __global__ __launch_bounds__(256) void router_select_kernel(const float* __restr
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int e = lane + 64 * i;
-      if (!((kept_groups >> (e < E ? e / epg : 0)) & 1ull)) key[i] = -INFINITY;
+      kept[i] = (kept_groups >> (e < E ? e / epg : 0)) & 1ull;
+      if (!kept[i]) key[i] = -INFINITY;
     }
   }
 
   if (k <= kArgmaxMaxK) {
-    // Small k: k rounds of a wave argmax over (key, expert index), each round
-    // taking the largest remaining key (the lower index on equal keys), so
-    // the experts come out in slot order (decreasing key) with no ordering
-    // step; lane j keeps slot j's expert and sigmoid score.
+    // Small k.  A key that is masked, taken or past E is 0, below the image of
+    // every float.  Lane j keeps slot j's expert.
+    uint32_t u[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) u[i] = lane + 64 * i < E && kept[i] ? ordered_bits(key[i]) : 0u;
     int my_e = 0;
-    float my_s = 0.0f;
     for (int j = 0; j < k; ++j) {
-      float bk = key[0];
-      int be = lane;
+      uint32_t m = u[0];
 #pragma unroll
-      for (int i = 1; i < PER; ++i)
-        if (key[i] > bk) {  // registers hold increasing indices: ties keep the lower one
-          bk = key[i];
-          be = lane + 64 * i;
-        }
-      wave_argmax(bk, be);  // every lane ends with the same best
-      float sv = s[0];
+      for (int i = 1; i < PER; ++i) m = max(m, u[i]);
+      m = wave_max(m);
+      int e = 0;
 #pragma unroll
-      for (int i = 1; i < PER; ++i)
-        if ((be >> 6) == i) sv = s[i];
-      sv = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, sv), be & 63));
-      if (lane == j) {
-        my_e = be;
-        my_s = sv;
+      for (int i = PER - 1; i >= 0; --i) {  // the lowest register, then the lowest lane that holds it
+        const unsigned long long at = __ballot(u[i] == m);
+        if (at) e = 64 * i + __ffsll((long long)at) - 1;
       }
 #pragma unroll
       for (int i = 0; i < PER; ++i)
-        if (lane + 64 * i == be) key[i] = -INFINITY;
+        if (lane + 64 * i == e) u[i] = 0u;
+      my_e = lane == j ? e : my_e;
     }
+    // Slot j's sigmoid score, and their sum in slot order.
+    float my_s = 0.0f;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const float v = __shfl(s[i], my_e & 63);
+      if ((my_e >> 6) == i) my_s = v;
+    }
+    float total = 0.0f;
+    for (int j = 0; j < k; ++j)
+      total += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, my_s), j));
     if (lane < k) {
       ids[t * k_out + lane] = my_e;
-      sel_s[slot][lane] = my_s;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (lane < k) {
-      float total = 0.0f;
-      for (int j = 0; j < k; ++j) total += sel_s[slot][j];
       wts[t * k_out + lane] = (my_s / total) * scaling;
     }
     if (shared >= 0 && lane == 0) {
@@ -544,8 +554,7 @@ constexpr int kRouterTiledMinTokens = 256;
 // kRouterMinChunk elements.
 int router_slices(int32_t T, int32_t H, int32_t E) {
   const bool tiled = T >= kRouterTiledMinTokens;
-  const int tm = router_tile_tokens(T);
-  const int64_t tiles = tiled ? ((int64_t)T + tm - 1) / tm * (((int64_t)E + kRtN - 1) / kRtN)
+  const int64_t tiles = tiled ? ((int64_t)T + kRtM - 1) / kRtM * (((int64_t)E + kRtN - 1) / kRtN)
                               : ((int64_t)T + 15) / 16 * (((int64_t)E + 255) / 256);
   const int64_t want = tiles >= 256 ? 1 : (256 + tiles - 1) / tiles;
   const int n32 = H / 32;
@@ -590,14 +599,9 @@ extern "C" moe_status_t moe_router(const uint16_t* x_bf16, int32_t T, int32_t H,
   const int ks = router_slices(T, H, E);
   float* part = static_cast<float*>(ws);
   if (T >= kRouterTiledMinTokens) {
-    const int tm = router_tile_tokens(T);
-    const dim3 grid((unsigned)((T + tm - 1) / tm), (unsigned)((E + kRtN - 1) / kRtN), (unsigned)ks);
-    if (tm == 256)
-      MOE_LAUNCH("router_logits", (router_logits_tiled_kernel<256, 3>), grid, dim3(512), 0, stream, x_bf16, T, H,
-                 w_router_bf16, E, H / ks, part);
-    else
-      MOE_LAUNCH("router_logits", (router_logits_tiled_kernel<128, 4>), grid, dim3(512), 0, stream, x_bf16, T, H,
-                 w_router_bf16, E, H / ks, part);
+    const dim3 grid((unsigned)ks, (unsigned)(((int64_t)T + kRtM - 1) / kRtM), (unsigned)((E + kRtN - 1) / kRtN));
+    MOE_LAUNCH("router_logits", router_logits_tiled_kernel, grid, dim3(512), 0, stream, x_bf16, T, H, w_router_bf16, E,
+               H / ks, part);
   } else {
     const dim3 grid((unsigned)((T + 15) / 16), (unsigned)((E + 255) / 256), (unsigned)ks);
     MOE_LAUNCH("router_logits", router_logits_kernel, grid, dim3(256), 0, stream, x_bf16, T, H, w_router_bf16, E,
