@@ -261,7 +261,7 @@ extern "C" moe_status_t moe_ffn_layer(moe_dims_t d, int32_t T, moe_regime_t regi
   float* y = reinterpret_cast<float*>(b + L.y);
   const size_t R = (size_t)T * d.topk;
 
-  if (rg == MOE_REGIME_DECODE && T == 1 && decode_down_combine_fits(d, T) && decode_one_token_fits(d)) {
+  if (rg == MOE_REGIME_DECODE && T == 1 && d.topk <= 16 && decode_down_combine_fits(d, T) && decode_one_token_fits(d)) {
     // One token: two launches and no prologue.  Gate/up quantizes the row
     // and reads the expert ids itself (row j of h is slot j); the down
     // projection and the combine follow in one launch.  The results are

@@ -1,5 +1,6 @@
 // Decode down projection fused with the router-weighted combine, for small
-// batches (R = T * k expert rows in all, R <= kDcMaxRows, K = I <= kDcMaxK).
+// batches (R = T * k expert rows in all, K = I <= kDcMaxK; see
+// decode_down_combine_fits).
 //
 // One workgroup owns 16 NT output columns [n0, n0 + 16 NT) of the layer and
 // computes them for every active expert, so the expert rows of the whole
@@ -23,15 +24,21 @@
 // with no barrier inside the loop.  At the end of each expert it stores the
 // expert's rows of its partial sum in LDS by expert row; after one barrier
 // the four partials of each row are summed in wave order.
+#include <algorithm>
+
 #include "common.h"
 
 namespace moe {
 
 namespace {
 
-constexpr int kDcMaxRows = 16;                // R = T * k (beyond, H / 16 workgroups stream too few bytes per CU)
+constexpr int kDcRows = 16;                   // R = T * k taken at any expert size (see decode_down_combine_fits)
+constexpr int kDcSmallRows = 64;              // R of layers with small experts
 constexpr int kDcMaxTokens = 16;              // rows of one expert: one 16-row MFMA operand
 constexpr int kDcMaxK = 2048;                 // I
+constexpr int kDcQhBytes = kDcRows * kDcMaxK; // the quantized h rows in LDS: R * I at most
+constexpr int kDcSmallBytes = 32 * 1024;      // W_down bytes of a workgroup that are latency rather than streaming
+constexpr int kDcFullHidden = 4096;           // H / 16 workgroups fill the 256 CUs
 constexpr int kDcMaxExperts = 1024;          // four 256-expert chunks of offsets
 
 struct DownCombineArgs {
@@ -141,18 +148,19 @@ __device__ __forceinline__ int active_slots(const int32_t* __restrict__ ids, int
 // loaded before the weight window (the rest, if R * K / 128 > 64 HQ, are
 // loaded after it); W: items in the weight window; NCH: 256-expert chunks
 // of the offsets (E <= 256 NCH); WAVES: 4 K parts x WAVES / 4 expert slots;
-// SLOT1: one token, experts from p.ids in slot order (active_slots).
-template <int NT, int HQ, int W, int NCH, int WAVES, bool SLOT1 = false>
+// MAXR: rows R at most; SLOT1: one token, experts from p.ids in slot order
+// (active_slots).
+template <int NT, int HQ, int W, int NCH, int WAVES, int MAXR, bool SLOT1 = false>
 __global__ __launch_bounds__(64 * WAVES) void ffn_decode_down_combine_kernel(DownCombineArgs p) {
   constexpr int kCols = 16 * NT;
   constexpr int kDcThreads = 64 * WAVES;
   constexpr int kSlots = WAVES / 4;
   static_assert(kSlots == 1 || kSlots == 2 || kSlots == 4, "expert slots: a power of two");
-  __shared__ __attribute__((aligned(16))) uint8_t qh[kDcMaxRows * kDcMaxK];
-  __shared__ float sh[kDcMaxRows * (kDcMaxK / kBlock)];
-  __shared__ float part[4 * kDcMaxRows * kCols];  // [K part][expert row][column]
-  __shared__ __attribute__((aligned(16))) float yl[kDcMaxRows * kCols];
-  __shared__ int32_t dest_id[SLOT1 ? kDcMaxRows : 1];  // SLOT1: slot j's row is row j
+  __shared__ __attribute__((aligned(16))) uint8_t qh[kDcQhBytes];
+  __shared__ float sh[kDcQhBytes / kBlock];
+  __shared__ float part[4 * MAXR * kCols];  // [K part][expert row][column]
+  __shared__ __attribute__((aligned(16))) float yl[MAXR * kCols];
+  __shared__ int32_t dest_id[SLOT1 ? MAXR : 1];  // SLOT1: slot j's row is row j
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -239,8 +247,8 @@ __global__ __launch_bounds__(64 * WAVES) void ffn_decode_down_combine_kernel(Dow
   }
   // Partials start at zero: a wave without K blocks (K < 512) adds +0.0, as
   // the decode down kernel's does.
-  for (int i = tid; i < 4 * kDcMaxRows * kCols; i += kDcThreads) part[i] = 0.0f;
-  if (SLOT1 && tid < kDcMaxRows) dest_id[tid] = tid;
+  for (int i = tid; i < 4 * MAXR * kCols; i += kDcThreads) part[i] = 0.0f;
+  if (SLOT1 && tid < MAXR) dest_id[tid] = tid;
   __syncthreads();
 
   v4f acc[NT];
@@ -270,7 +278,7 @@ __global__ __launch_bounds__(64 * WAVES) void ffn_decode_down_combine_kernel(Dow
           for (int i = 0; i < 4; ++i) acc[nt][i] += d[i] * (sa[i] * ws);
         }
         if (j == nkw - 1) {  // the expert's last block: keep its rows, restart
-          float* dst = part + kw * kDcMaxRows * kCols;
+          float* dst = part + kw * MAXR * kCols;
 #pragma unroll
           for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -288,9 +296,9 @@ __global__ __launch_bounds__(64 * WAVES) void ffn_decode_down_combine_kernel(Dow
   // Rows of the active experts: the four K parts summed in wave order.
   for (int i = tid; i < R * kCols; i += kDcThreads) {
     float v = part[i];
-    v += part[kDcMaxRows * kCols + i];
-    v += part[2 * kDcMaxRows * kCols + i];
-    v += part[3 * kDcMaxRows * kCols + i];
+    v += part[MAXR * kCols + i];
+    v += part[2 * MAXR * kCols + i];
+    v += part[3 * MAXR * kCols + i];
     yl[i] = v;
   }
   __syncthreads();
@@ -308,10 +316,23 @@ __global__ __launch_bounds__(64 * WAVES) void ffn_decode_down_combine_kernel(Dow
 
 }  // namespace
 
-// True when the fused down + combine takes this batch.
+// True when the fused down + combine takes this batch.  Against the separate
+// launches (quantize h, down, combine; rocprofv3, fused first):
+//   up to 16 rows always (the h rows of I <= 2048 fit in LDS);
+//   17 to 64 rows whose h rows fit in the same LDS, if the H / 16 workgroups
+//   fill the chip (H 4096, I 1536, 9 tokens x 2: 18.7 against 25.0 us; H 7168,
+//   I 1024, 3 x 8: 34.6 against 37.6) or have so little to stream that the
+//   launches are what counts (H 256, I 128, 16 x 2: 7.5 against 9.1 us, and
+//   two launches fewer for the host); not with half the CUs idle (H 2048, I
+//   768, 3 x 8: 18.0 against 15.6 us) or more to stream (H 1024, I 512, 16 x
+//   4: 14.9 against 11.8 us).
+// 2048-wide experts beyond 16 rows lose by the bytes: 32 rows 99 against 90 us.
 bool decode_down_combine_fits(const moe_dims_t& d, int32_t T) {
-  return T >= 1 && T <= kDcMaxTokens && (int64_t)T * d.topk <= kDcMaxRows && d.inter <= kDcMaxK &&
-         d.n_experts <= kDcMaxExperts && d.hidden % 32 == 0;
+  const int64_t R = (int64_t)T * d.topk;
+  if (T < 1 || T > kDcMaxTokens || R > kDcSmallRows || R * d.inter > kDcQhBytes || d.inter > kDcMaxK ||
+      d.n_experts > kDcMaxExperts || d.hidden % 32)
+    return false;
+  return R <= kDcRows || d.hidden >= kDcFullHidden || std::min<int64_t>(R, d.n_experts) * d.inter * 16 <= kDcSmallBytes;
 }
 
 // y = down(h) of every active expert combined per token into out (bf16 [T, H]).
@@ -319,8 +340,7 @@ moe_status_t run_ffn_decode_down_combine(const moe_dims_t& d, int32_t T, const f
                                          const uint8_t* w_down, const float* s_down, const int32_t* dest_row,
                                          const float* topk_w, uint16_t* out, hipStream_t stream) {
   if (!decode_down_combine_fits(d, T))
-    return fail(MOE_ERR_UNSUPPORTED_SHAPE, "decode down+combine: T=%d (max %d), T*k=%d (max %d), I=%d (max %d)", T,
-                kDcMaxTokens, T * d.topk, kDcMaxRows, d.inter, kDcMaxK);
+    return fail(MOE_ERR_UNSUPPORTED_SHAPE, "decode down+combine: T=%d k=%d I=%d", T, d.topk, d.inter);
   DownCombineArgs a{};
   a.h = h; a.offsets = offsets; a.E = d.n_experts;
   a.w = w_down; a.s = s_down; a.N = d.hidden; a.K = d.inter;
@@ -330,12 +350,18 @@ moe_status_t run_ffn_decode_down_combine(const moe_dims_t& d, int32_t T, const f
   // them are resident at once on all CUs (at H = 7168: 448 on 256 CUs; 224
   // workgroups of 32 columns left 32 CUs idle).  Four h row blocks per lane
   // group go out ahead of the weight window; any others follow it.
-  if (d.n_experts <= 256)
-    MOE_LAUNCH("ffn_decode_down_combine", (ffn_decode_down_combine_kernel<1, 4, 4, 1, 8>),
-               dim3((unsigned)(d.hidden / 16)), dim3(512), 0, stream, a);
-  else
-    MOE_LAUNCH("ffn_decode_down_combine", (ffn_decode_down_combine_kernel<1, 4, 4, kDcMaxExperts / 256, 8>),
-               dim3((unsigned)(d.hidden / 16)), dim3(512), 0, stream, a);
+#define MOE_DC_LAUNCH(NCH, MAXR)                                                                       \
+  MOE_LAUNCH("ffn_decode_down_combine", (ffn_decode_down_combine_kernel<1, 4, 4, NCH, 8, MAXR>),        \
+             dim3((unsigned)(d.hidden / 16)), dim3(512), 0, stream, a)
+  constexpr int kAllChunks = kDcMaxExperts / 256;
+  if (T * d.topk <= kDcRows) {
+    if (d.n_experts <= 256) MOE_DC_LAUNCH(1, kDcRows);
+    else MOE_DC_LAUNCH(kAllChunks, kDcRows);
+  } else {
+    if (d.n_experts <= 256) MOE_DC_LAUNCH(1, kDcSmallRows);
+    else MOE_DC_LAUNCH(kAllChunks, kDcSmallRows);
+  }
+#undef MOE_DC_LAUNCH
   return check_launch("ffn_decode_down_combine");
 }
 
@@ -345,14 +371,13 @@ moe_status_t run_ffn_decode_down_combine(const moe_dims_t& d, int32_t T, const f
 moe_status_t run_ffn_decode_down_combine_one_token(const moe_dims_t& d, const float* h, const int32_t* topk_ids,
                                                    const uint8_t* w_down, const float* s_down, const float* topk_w,
                                                    uint16_t* out, hipStream_t stream) {
-  if (!decode_down_combine_fits(d, 1))
-    return fail(MOE_ERR_UNSUPPORTED_SHAPE, "decode down+combine: k=%d (max %d), I=%d (max %d)", d.topk, kDcMaxRows,
-                d.inter, kDcMaxK);
+  if (d.topk > kDcRows || !decode_down_combine_fits(d, 1))
+    return fail(MOE_ERR_UNSUPPORTED_SHAPE, "decode down+combine: k=%d I=%d", d.topk, d.inter);
   DownCombineArgs a{};
   a.h = h; a.ids = topk_ids; a.E = d.n_experts;
   a.w = w_down; a.s = s_down; a.N = d.hidden; a.K = d.inter;
   a.topk_w = topk_w; a.topk = d.topk; a.tokens = 1; a.out = out;
-  MOE_LAUNCH("ffn_decode_down_combine", (ffn_decode_down_combine_kernel<1, 4, 4, 1, 8, true>),
+  MOE_LAUNCH("ffn_decode_down_combine", (ffn_decode_down_combine_kernel<1, 4, 4, 1, 8, kDcRows, true>),
              dim3((unsigned)(d.hidden / 16)), dim3(512), 0, stream, a);
   return check_launch("ffn_decode_down_combine");
 }
