@@ -22,28 +22,35 @@ from ._lib import (  # noqa: F401
 from ._lib import check as _check
 
 
-def _ptr(t):
-    return ctypes.c_void_p(0 if t is None else t.data_ptr())
-
-
 def _stream(stream):
+    """The HIP stream to launch on: the caller's, or the current device's current stream.
+
+    A small call is bound by the host, so the current stream's handle is taken
+    without building a torch Stream object (0.2 us instead of 2.9) where torch
+    has initialised the device in this process already."""
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _nbytes(t):
     return 0 if t is None else t.numel() * t.element_size()
 
 
-def _need(t, dtype_bytes, name):
-    if t is not None:
-        if not t.is_cuda:
-            raise ValueError(f"{name} must be a device tensor")
-        if not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous")
-        if t.element_size() != dtype_bytes:
-            raise ValueError(f"{name} has element size {t.element_size()}, expected {dtype_bytes}")
+def _dev(t, dtype_bytes, name):
+    """The address of a contiguous device tensor of dtype_bytes-byte elements (0 for None)."""
+    if t is None:
+        return 0
+    if not t.is_cuda:
+        raise ValueError(f"{name} must be a device tensor")
+    if not t.is_contiguous():
+        raise ValueError(f"{name} must be contiguous")
+    if t.element_size() != dtype_bytes:
+        raise ValueError(f"{name} has element size {t.element_size()}, expected {dtype_bytes}")
+    return t.data_ptr()
 
 
 def moe_status_string(status: int) -> str:
@@ -56,31 +63,31 @@ def moe_last_error() -> str:
 
 def moe_quant_act(x_bf16, q, s, stream=None):
     """x_bf16 [rows, cols] (bf16 or 16-bit view) -> q uint8 [rows, cols], s fp32 [rows, cols/128]."""
-    _need(x_bf16, 2, "x_bf16"); _need(q, 1, "q"); _need(s, 4, "s")
+    px, pq, ps = _dev(x_bf16, 2, "x_bf16"), _dev(q, 1, "q"), _dev(s, 4, "s")
     rows, cols = x_bf16.shape
-    _check(lib.moe_quant_act(_ptr(x_bf16), rows, cols, _ptr(q), _ptr(s), _stream(stream)))
+    _check(lib.moe_quant_act(px, rows, cols, pq, ps, _stream(stream)))
 
 
 def moe_quant_rows_f32(x, q, s, stream=None):
-    _need(x, 4, "x"); _need(q, 1, "q"); _need(s, 4, "s")
+    px, pq, ps = _dev(x, 4, "x"), _dev(q, 1, "q"), _dev(s, 4, "s")
     rows, cols = x.shape
-    _check(lib.moe_quant_rows_f32(_ptr(x), rows, cols, _ptr(q), _ptr(s), _stream(stream)))
+    _check(lib.moe_quant_rows_f32(px, rows, cols, pq, ps, _stream(stream)))
 
 
 def moe_quant_weight(w, q, s, stream=None):
     """w fp32 [n_mats, rows, cols] (or [rows, cols]) -> q uint8 same shape, s fp32 [.., rows/128, cols/128]."""
-    _need(w, 4, "w"); _need(q, 1, "q"); _need(s, 4, "s")
+    pw, pq, ps = _dev(w, 4, "w"), _dev(q, 1, "q"), _dev(s, 4, "s")
     shape = w.shape if w.dim() == 3 else (1, *w.shape)
-    _check(lib.moe_quant_weight(_ptr(w), shape[0], shape[1], shape[2], _ptr(q), _ptr(s), _stream(stream)))
+    _check(lib.moe_quant_weight(pw, shape[0], shape[1], shape[2], pq, ps, _stream(stream)))
 
 
 def moe_pack_weight(q, packed, stream=None):
     """q uint8 [n_mats, rows, cols] (or [rows, cols]) row-major -> packed operand tiles (same size)."""
-    _need(q, 1, "q"); _need(packed, 1, "packed")
+    pq, pp = _dev(q, 1, "q"), _dev(packed, 1, "packed")
     shape = q.shape if q.dim() == 3 else (1, *q.shape)
     if packed.numel() != q.numel():
         raise MoEError(MOE_ERR_INVALID_ARG, "moe_pack_weight: packed must have as many bytes as q")
-    _check(lib.moe_pack_weight(_ptr(q), shape[0], shape[1], shape[2], _ptr(packed), _stream(stream)))
+    _check(lib.moe_pack_weight(pq, shape[0], shape[1], shape[2], pp, _stream(stream)))
 
 
 def moe_permute_workspace(T: int, k: int, E: int) -> int:
@@ -89,28 +96,28 @@ def moe_permute_workspace(T: int, k: int, E: int) -> int:
 
 def moe_permute(topk_ids, n_experts, expert_offsets, sorted_src, dest_row, dev_status=None, ws=None,
                 stream=None):
-    _need(topk_ids, 4, "topk_ids"); _need(expert_offsets, 4, "expert_offsets")
-    _need(sorted_src, 4, "sorted_src"); _need(dest_row, 4, "dest_row")
-    _need(dev_status, 4, "dev_status"); _need(ws, 1, "ws")
+    ids, off = _dev(topk_ids, 4, "topk_ids"), _dev(expert_offsets, 4, "expert_offsets")
+    src, dst = _dev(sorted_src, 4, "sorted_src"), _dev(dest_row, 4, "dest_row")
+    st, pws = _dev(dev_status, 4, "dev_status"), _dev(ws, 1, "ws")
     T, k = topk_ids.shape
-    _check(lib.moe_permute(_ptr(topk_ids), T, k, n_experts, _ptr(expert_offsets), _ptr(sorted_src),
-                           _ptr(dest_row), _ptr(dev_status), _ptr(ws), _nbytes(ws), _stream(stream)))
+    _check(lib.moe_permute(ids, T, k, n_experts, off, src, dst, st, pws, _nbytes(ws), _stream(stream)))
 
 
 def moe_expert_ffn_workspace(dims: MoeDims, T: int, regime: int = MOE_REGIME_AUTO) -> int:
     return int(lib.moe_expert_ffn_workspace(dims, T, regime))
 
 
+def _weights(w_gate, s_gate, w_up, s_up, w_down, s_down):
+    return (_dev(w_gate, 1, "w_gate"), _dev(s_gate, 4, "s_gate"), _dev(w_up, 1, "w_up"), _dev(s_up, 4, "s_up"),
+            _dev(w_down, 1, "w_down"), _dev(s_down, 4, "s_down"))
+
+
 def moe_expert_ffn(dims: MoeDims, T: int, regime: int, qx, sx, expert_offsets, sorted_src,
                    w_gate, s_gate, w_up, s_up, w_down, s_down, y_rows, ws, stream=None):
-    for t, nb, n in ((qx, 1, "qx"), (sx, 4, "sx"), (expert_offsets, 4, "expert_offsets"),
-                     (sorted_src, 4, "sorted_src"), (w_gate, 1, "w_gate"), (s_gate, 4, "s_gate"),
-                     (w_up, 1, "w_up"), (s_up, 4, "s_up"), (w_down, 1, "w_down"), (s_down, 4, "s_down"),
-                     (y_rows, 4, "y_rows"), (ws, 1, "ws")):
-        _need(t, nb, n)
-    _check(lib.moe_expert_ffn(dims, T, regime, _ptr(qx), _ptr(sx), _ptr(expert_offsets), _ptr(sorted_src),
-                              _ptr(w_gate), _ptr(s_gate), _ptr(w_up), _ptr(s_up), _ptr(w_down),
-                              _ptr(s_down), _ptr(y_rows), _ptr(ws), _nbytes(ws), _stream(stream)))
+    args = (_dev(qx, 1, "qx"), _dev(sx, 4, "sx"), _dev(expert_offsets, 4, "expert_offsets"),
+            _dev(sorted_src, 4, "sorted_src"), *_weights(w_gate, s_gate, w_up, s_up, w_down, s_down),
+            _dev(y_rows, 4, "y_rows"), _dev(ws, 1, "ws"))
+    _check(lib.moe_expert_ffn(dims, T, regime, *args, _nbytes(ws), _stream(stream)))
 
 
 def moe_expert_ffn_w8a16_workspace(dims: MoeDims, T: int) -> int:
@@ -120,13 +127,9 @@ def moe_expert_ffn_w8a16_workspace(dims: MoeDims, T: int) -> int:
 def moe_expert_ffn_w8a16(dims: MoeDims, T: int, x_bf16, expert_offsets, sorted_src,
                          w_gate, s_gate, w_up, s_up, w_down, s_down, y_rows, ws, stream=None):
     """Decode-regime expert FFN with bf16 activations (the W8A16 GEMV numerics)."""
-    for t, nb, n in ((x_bf16, 2, "x_bf16"), (expert_offsets, 4, "expert_offsets"), (sorted_src, 4, "sorted_src"),
-                     (w_gate, 1, "w_gate"), (s_gate, 4, "s_gate"), (w_up, 1, "w_up"), (s_up, 4, "s_up"),
-                     (w_down, 1, "w_down"), (s_down, 4, "s_down"), (y_rows, 4, "y_rows"), (ws, 1, "ws")):
-        _need(t, nb, n)
-    _check(lib.moe_expert_ffn_w8a16(dims, T, _ptr(x_bf16), _ptr(expert_offsets), _ptr(sorted_src), _ptr(w_gate),
-                                    _ptr(s_gate), _ptr(w_up), _ptr(s_up), _ptr(w_down), _ptr(s_down), _ptr(y_rows),
-                                    _ptr(ws), _nbytes(ws), _stream(stream)))
+    args = (_dev(x_bf16, 2, "x_bf16"), _dev(expert_offsets, 4, "expert_offsets"), _dev(sorted_src, 4, "sorted_src"),
+            *_weights(w_gate, s_gate, w_up, s_up, w_down, s_down), _dev(y_rows, 4, "y_rows"), _dev(ws, 1, "ws"))
+    _check(lib.moe_expert_ffn_w8a16(dims, T, *args, _nbytes(ws), _stream(stream)))
 
 
 def moe_router_workspace(T: int, H: int, E: int) -> int:
@@ -138,25 +141,23 @@ def moe_router(x_bf16, w_router_bf16, bias, topk_ids, topk_w, n_group=1, topk_gr
     """x_bf16 [T, H], w_router_bf16 [E, H] (bf16 or 16-bit views), bias fp32 [E] or None
     -> topk_ids int32 [T, k], topk_w fp32 [T, k]; with shared_expert >= 0 both are
     [T, k + 1] and the last slot is (shared_expert, 1.0)."""
-    _need(x_bf16, 2, "x_bf16"); _need(w_router_bf16, 2, "w_router_bf16"); _need(bias, 4, "bias")
-    _need(topk_ids, 4, "topk_ids"); _need(topk_w, 4, "topk_w"); _need(ws, 1, "ws")
+    px, pw, pb = _dev(x_bf16, 2, "x_bf16"), _dev(w_router_bf16, 2, "w_router_bf16"), _dev(bias, 4, "bias")
+    ids, wts, pws = _dev(topk_ids, 4, "topk_ids"), _dev(topk_w, 4, "topk_w"), _dev(ws, 1, "ws")
     T, H = x_bf16.shape
     E = w_router_bf16.shape[0]
     k = topk_ids.shape[1] - (1 if shared_expert >= 0 else 0)
     if topk_w.shape != topk_ids.shape:
         raise ValueError("topk_w must have the shape of topk_ids")
     cfg = MoeRouterCfg(n_group, topk_group, routed_scaling, shared_expert)
-    _check(lib.moe_router(_ptr(x_bf16), T, H, _ptr(w_router_bf16), _ptr(bias), E, k, cfg, _ptr(topk_ids),
-                          _ptr(topk_w), _ptr(ws), _nbytes(ws), _stream(stream)))
+    _check(lib.moe_router(px, T, H, pw, pb, E, k, cfg, ids, wts, pws, _nbytes(ws), _stream(stream)))
 
 
 def moe_combine(y_rows, dest_row, topk_w, out_bf16, stream=None):
-    _need(y_rows, 4, "y_rows"); _need(dest_row, 4, "dest_row"); _need(topk_w, 4, "topk_w")
-    _need(out_bf16, 2, "out_bf16")
+    y, dst, w = _dev(y_rows, 4, "y_rows"), _dev(dest_row, 4, "dest_row"), _dev(topk_w, 4, "topk_w")
+    out = _dev(out_bf16, 2, "out_bf16")
     T, k = topk_w.shape
     H = out_bf16.shape[1]
-    _check(lib.moe_combine(_ptr(y_rows), _ptr(dest_row), _ptr(topk_w), T, k, H, _ptr(out_bf16),
-                           _stream(stream)))
+    _check(lib.moe_combine(y, dst, w, T, k, H, out, _stream(stream)))
 
 
 def moe_ffn_layer_workspace(dims: MoeDims, T: int, regime: int = MOE_REGIME_AUTO) -> int:
@@ -166,27 +167,19 @@ def moe_ffn_layer_workspace(dims: MoeDims, T: int, regime: int = MOE_REGIME_AUTO
 def moe_ffn_layer(dims: MoeDims, T: int, regime: int, x_bf16, topk_ids, topk_w, w_gate, s_gate, w_up, s_up,
                   w_down, s_down, out_bf16, dev_status, ws, stream=None):
     """The whole resident layer in one library call (see include/moe.h)."""
-    for t, nb, n in ((x_bf16, 2, "x_bf16"), (topk_ids, 4, "topk_ids"), (topk_w, 4, "topk_w"),
-                     (w_gate, 1, "w_gate"), (s_gate, 4, "s_gate"), (w_up, 1, "w_up"), (s_up, 4, "s_up"),
-                     (w_down, 1, "w_down"), (s_down, 4, "s_down"), (out_bf16, 2, "out_bf16"),
-                     (dev_status, 4, "dev_status"), (ws, 1, "ws")):
-        _need(t, nb, n)
-    _check(lib.moe_ffn_layer(dims, T, regime, _ptr(x_bf16), _ptr(topk_ids), _ptr(topk_w), _ptr(w_gate),
-                             _ptr(s_gate), _ptr(w_up), _ptr(s_up), _ptr(w_down), _ptr(s_down), _ptr(out_bf16),
-                             _ptr(dev_status), _ptr(ws), _nbytes(ws), _stream(stream)))
+    args = (_dev(x_bf16, 2, "x_bf16"), _dev(topk_ids, 4, "topk_ids"), _dev(topk_w, 4, "topk_w"),
+            *_weights(w_gate, s_gate, w_up, s_up, w_down, s_down), _dev(out_bf16, 2, "out_bf16"),
+            _dev(dev_status, 4, "dev_status"), _dev(ws, 1, "ws"))
+    _check(lib.moe_ffn_layer(dims, T, regime, *args, _nbytes(ws), _stream(stream)))
 
 
 def moe_ffn_layer_noalloc(dims: MoeDims, T: int, regime: int, x_bf16, topk_ids, topk_w, w_gate, s_gate, w_up, s_up,
                           w_down, s_down, out_bf16, dev_status=None, stream=None):
     """moe_ffn_layer with the library's per-GPU scratch array instead of a workspace (see include/moe.h)."""
-    for t, nb, n in ((x_bf16, 2, "x_bf16"), (topk_ids, 4, "topk_ids"), (topk_w, 4, "topk_w"),
-                     (w_gate, 1, "w_gate"), (s_gate, 4, "s_gate"), (w_up, 1, "w_up"), (s_up, 4, "s_up"),
-                     (w_down, 1, "w_down"), (s_down, 4, "s_down"), (out_bf16, 2, "out_bf16"),
-                     (dev_status, 4, "dev_status")):
-        _need(t, nb, n)
-    _check(lib.moe_ffn_layer_noalloc(dims, T, regime, _ptr(x_bf16), _ptr(topk_ids), _ptr(topk_w), _ptr(w_gate),
-                                     _ptr(s_gate), _ptr(w_up), _ptr(s_up), _ptr(w_down), _ptr(s_down),
-                                     _ptr(out_bf16), _ptr(dev_status), _stream(stream)))
+    args = (_dev(x_bf16, 2, "x_bf16"), _dev(topk_ids, 4, "topk_ids"), _dev(topk_w, 4, "topk_w"),
+            *_weights(w_gate, s_gate, w_up, s_up, w_down, s_down), _dev(out_bf16, 2, "out_bf16"),
+            _dev(dev_status, 4, "dev_status"))
+    _check(lib.moe_ffn_layer_noalloc(dims, T, regime, *args, _stream(stream)))
 
 
 class StreamContext:
@@ -241,11 +234,12 @@ def moe_stream_schedule(dims: MoeDims, T: int, chunk_tokens: int, ring_slots: in
     return [(o.op, o.a, o.b, o.c) for o in ops[:n.value]], bytes(rec)
 
 
-def _need_pinned(t, dtype_bytes, name):
+def _pinned(t, dtype_bytes, name):
     if t.is_cuda or not t.is_pinned():
         raise ValueError(f"{name} must be a pinned host tensor")
     if not t.is_contiguous() or t.element_size() != dtype_bytes:
         raise ValueError(f"{name} must be contiguous with element size {dtype_bytes}")
+    return t.data_ptr()
 
 
 def moe_ffn_streamed(dims: MoeDims, chunk_tokens: int, x_bf16, topk_ids, topk_w, host_weights, dev_ring,
@@ -253,20 +247,20 @@ def moe_ffn_streamed(dims: MoeDims, chunk_tokens: int, x_bf16, topk_ids, topk_w,
                      copy_stream=None):
     """host_weights = (w_gate, s_gate, w_up, s_up, w_down, s_down) pinned host tensors."""
     T = x_bf16.shape[0]
-    _need(x_bf16, 2, "x_bf16"); _need(topk_ids, 4, "topk_ids"); _need(topk_w, 4, "topk_w")
-    _need(dev_ring, 1, "dev_ring"); _need(dev_ring_scales, 4, "dev_ring_scales")
-    _need(out_bf16, 2, "out_bf16"); _need(dev_status, 4, "dev_status"); _need(ws, 1, "ws")
-    for t, nb, n in zip(host_weights, (1, 4, 1, 4, 1, 4),
-                        ("host_w_gate", "host_s_gate", "host_w_up", "host_s_up", "host_w_down", "host_s_down")):
-        _need_pinned(t, nb, n)
+    px, ids, w = _dev(x_bf16, 2, "x_bf16"), _dev(topk_ids, 4, "topk_ids"), _dev(topk_w, 4, "topk_w")
+    ring, ring_s = _dev(dev_ring, 1, "dev_ring"), _dev(dev_ring_scales, 4, "dev_ring_scales")
+    out, st, pws = _dev(out_bf16, 2, "out_bf16"), _dev(dev_status, 4, "dev_status"), _dev(ws, 1, "ws")
+    if len(host_weights) != 6:
+        raise ValueError("host_weights must hold six tensors")
+    hw = [_pinned(t, nb, n) for t, nb, n in zip(
+        host_weights, (1, 4, 1, 4, 1, 4),
+        ("host_w_gate", "host_s_gate", "host_w_up", "host_s_up", "host_w_down", "host_s_down"))]
     if dev_ring.numel() < moe_ring_bytes(dims, ctx.slots):
         raise ValueError("dev_ring is smaller than moe_ring_bytes(dims, ctx.slots)")
     if dev_ring_scales.numel() * 4 < moe_ring_scale_bytes(dims, ctx.slots):
         raise ValueError("dev_ring_scales is smaller than moe_ring_scale_bytes(dims, ctx.slots)")
-    hw = [_ptr(t) for t in host_weights]
-    _check(lib.moe_ffn_streamed(dims, T, chunk_tokens, _ptr(x_bf16), _ptr(topk_ids), _ptr(topk_w), *hw,
-                                _ptr(dev_ring), _ptr(dev_ring_scales), ctx.handle, _ptr(out_bf16), _ptr(dev_status),
-                                _ptr(ws), _nbytes(ws), _stream(compute_stream), _stream(copy_stream)))
+    _check(lib.moe_ffn_streamed(dims, T, chunk_tokens, px, ids, w, *hw, ring, ring_s, ctx.handle, out, st, pws,
+                                _nbytes(ws), _stream(compute_stream), _stream(copy_stream)))
 
 
 def moe_profile_begin(max_launches: int) -> None:

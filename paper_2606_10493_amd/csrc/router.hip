@@ -559,8 +559,8 @@ int router_slices(int32_t T, int32_t H, int32_t E) {
   const int64_t want = tiles >= 256 ? 1 : (256 + tiles - 1) / tiles;
   const int n32 = H / 32;
   int best = 1;
-  for (int ks = 1; ks <= n32; ++ks)
-    if (n32 % ks == 0 && (int64_t)ks <= want && (H / ks) >= kRouterMinChunk) best = ks;
+  for (int ks = 1; ks <= n32 && ks <= want; ++ks)
+    if (n32 % ks == 0 && (H / ks) >= kRouterMinChunk) best = ks;
   return best;
 }
 
