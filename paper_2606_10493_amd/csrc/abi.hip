@@ -59,7 +59,7 @@ moe_status_t launch_layer_prologue(const uint16_t* x, int32_t T, int32_t H, cons
                                    int32_t* dest_row, int32_t* dev_status, const TilesOut& tiles, void* perm_ws,
                                    hipStream_t stream);
 bool layer_prologue_writes_tiles(int32_t T, int32_t k);
-TilesOut prefill_tiles_out(const moe_dims_t& d, int32_t T, int32_t* tiles);
+TilesOut prefill_tiles_out(const moe_dims_t& d, int32_t T, const float* sx, int32_t* tiles);
 
 moe_status_t run_ffn_prefill(const moe_dims_t& d, int32_t T, const uint8_t* qx, const float* sx,
                              const int32_t* offsets, const int32_t* sorted_src, const uint8_t* w_gate,
@@ -280,7 +280,7 @@ extern "C" moe_status_t moe_ffn_layer(moe_dims_t d, int32_t T, moe_regime_t regi
   const bool tiles_ready = rg == MOE_REGIME_PREFILL && layer_prologue_writes_tiles(T, d.topk);
   st = launch_layer_prologue(x_bf16, T, d.hidden, topk_ids, d.topk, d.n_experts, qx, sx, offsets, sorted_src, dest_row,
                              dev_status,
-                             tiles_ready ? prefill_tiles_out(d, T, reinterpret_cast<int32_t*>(rest)) : TilesOut{},
+                             tiles_ready ? prefill_tiles_out(d, T, sx, reinterpret_cast<int32_t*>(rest)) : TilesOut{},
                              b + L.perm, stream);
   if (st != MOE_OK) return st;
 

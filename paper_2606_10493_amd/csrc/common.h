@@ -280,6 +280,17 @@ __device__ __forceinline__ void async_load_1k(const void* src, uint32_t lds) {
                : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(src)
                : "memory");
 }
+// The same from base + offset (base uniform, offset the lane's) if `on`
+// (uniform), without a branch that the compiler sees: between matrix
+// instructions a basic block's end costs it the registers' order.
+__device__ __forceinline__ void async_load_1k_if(int on, const void* base, uint32_t offset, uint32_t lds) {
+  asm volatile("s_cmp_eq_u32 %3, 0\n\ts_cbranch_scc1 .Lmoe_skip_%=\n\t"
+               "s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n.Lmoe_skip_%=:"
+               :
+               : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(offset), "s"(base),
+                 "s"(__builtin_amdgcn_readfirstlane(on))
+               : "memory", "scc");
+}
 // Waits until at most N of this wave's newest loads and stores are
 // outstanding and its LDS operations are done, then the workgroup barrier.
 template <int N>
@@ -314,18 +325,23 @@ struct PrefillRows {
   int chunk_tokens;
   int32_t tokens;       // activation rows of the gate/up projections (all chunks)
   int64_t rows;         // sorted rows of all chunks (activation rows of the down projection)
+  int64_t unit_rows;    // expected rows of the launch's n_units experts (all of `rows` for a resident layer)
   int64_t max_mtiles;   // bound on the launch's 128-row m-tiles (sizes the grid and the descriptor table)
   bool tiles_ready;     // the m-tile table is written already (one chunk only)
 };
 
-// Expert rows per prefill m-tile, and the m-tile table of a launch over one
+// Expert rows per prefill m-tile (of the two GEMM kernels), and the m-tile table of a launch over one
 // chunk of rows (see prefill_tiles_kernel): written by the layer's sort, which
 // knows the experts' counts, or by prefill_tiles_kernel.
-constexpr int kPrefillTileRows = 128;
+constexpr int kPrefillTileRows = 128, kPrefillWideRows = 256;
+constexpr int kXcd = 8;
+constexpr int kQueueInts = 2 * kXcd;  // work-queue counters of the two GEMMs
 struct TilesOut {
   int32_t* mtile_start;  // [E+1]; NULL: no table wanted
+  int32_t* queue;        // [kQueueInts], zeroed
   int4* desc;            // [max_mtiles]
   int64_t max_mtiles;
+  int tile_rows;         // kPrefillTileRows or kPrefillWideRows
 };
 
 void set_error(const char* fmt, ...);

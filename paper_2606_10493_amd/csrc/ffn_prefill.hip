@@ -47,7 +47,7 @@
 // (read from the tile scan; the grid is only an upper bound) item = (block
 // % 8) * ceil(n / 8) + block / 8 keeps an expert's items on one XCD's L2
 // while every XCD gets an equal share.
-#include "common.h"
+#include "ffn_prefill.h"
 
 #include <type_traits>
 
@@ -56,41 +56,15 @@ namespace moe {
 namespace {
 
 constexpr int kBM = kPrefillTileRows;   // expert rows (tokens) per tile
-constexpr int kBN = 256;                // weight rows per tile
+constexpr int kBN = kPrefillWeightRows; // weight rows per tile
 constexpr int kThreads = 512;           // 8 waves x 32 weight rows
 constexpr int kLdsRow = kBlock;         // LDS row (bytes); 16-byte chunks XOR-swizzled, see swz()
 constexpr int kHalf = kBM * kLdsRow;    // one K block of the expert rows (one LDS stage)
 constexpr int kStages = 3;              // LDS stages of the ping-pong pipeline
 constexpr int kSaStride = kBM + 1;      // floats per K block of the row-scale table
 constexpr int kRing = 3;                // weight K blocks in registers
-constexpr int kXcd = 8;
-constexpr int kBand = 8;                // m-tiles per band of the work-item order (see tile_of)
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-
-struct PrefillArgs {
-  const uint8_t* a;           // e4m3 activations [a_rows, K]
-  const float* sa;            // [a_rows, K/128]
-  const int32_t* sorted_src;  // GATEUP without row tables: A row of sorted row p = sorted_src[p] / topk; else unused
-  const int32_t* row_pos;     // NULL: tile rows are sorted positions; else the sorted position of launch row v
-  const int32_t* row_tok;     // GATEUP with row_pos: the token (A row) of launch row v
-  int topk;
-  int a_rows;
-  const int32_t* mtile_start; // [n_units+1] exclusive scan of the experts' m-tile counts
-  const int4* desc;           // [max_mtiles] m-tile block descriptors (prefill_tiles_kernel)
-  int64_t max_mtiles;         // bound on the m-tiles (sizes desc)
-  int n_units;                // experts of the launch
-  const uint8_t* w0;          // GATEUP: W_gate [E, N, K]; DOWN: W_down [E, N, K]; packed tiles
-  const float* s0;
-  const uint8_t* w1;          // GATEUP: W_up, packed tiles
-  const float* s1;
-  int N, K;                   // N: output columns of the expert (I for gate/up, H for down)
-  int n_tiles;                // GATEUP: N/128; DOWN: N/256
-  float* y;                   // DOWN output fp32 [rows, N]
-  uint8_t* qh;                // GATEUP output e4m3 [rows, N]
-  float* sh;                  // GATEUP output [rows, N/128]
-};
 
 // The rows of a launch.  One chunk (a resident layer): expert u owns the
 // sorted positions [offsets[u], offsets[u+1]).  Several chunks, each sorted
@@ -100,7 +74,7 @@ struct PrefillArgs {
 // order (prefill_rows_kernel maps each launch row to its sorted position and
 // token), so the tiles of an expert span chunks and all of them read the
 // expert's weight slices together.  mtile_start = exclusive scan of the
-// experts' m-tile counts ceil(M_u / 128), and for every m-tile index b in
+// experts' m-tile counts ceil(M_u / tile_rows), and for every m-tile index b in
 // [mtile_start[u], mtile_start[u+1]) desc[b] = (u, mtile_start[u], first
 // row, end row), from which a GEMM workgroup derives its tile with one
 // uniform load (no search).  Experts are taken 1024 at a time with running
@@ -109,7 +83,9 @@ __global__ __launch_bounds__(1024) void prefill_tiles_kernel(const int32_t* __re
                                                              int n_units, int n_chunks,
                                                              int32_t* __restrict__ mtile_start,
                                                              int32_t* __restrict__ vstart,
-                                                             int4* __restrict__ desc, int64_t max_mtiles) {
+                                                             int32_t* __restrict__ queue,
+                                                             int4* __restrict__ desc, int64_t max_mtiles,
+                                                             int tile_rows) {
   __shared__ int wave_tot[16];
   int carry_t = 0, carry_v = 0;
   for (int base = 0; base < n_units; base += 1024) {
@@ -123,7 +99,7 @@ __global__ __launch_bounds__(1024) void prefill_tiles_kernel(const int32_t* __re
         for (int c = 0; c < n_chunks; ++c) m += offsets[c * off_stride + u + 1] - offsets[c * off_stride + u];
       }
     }
-    const int cnt = m > 0 ? (m + kBM - 1) / kBM : 0;
+    const int cnt = m > 0 ? (m + tile_rows - 1) / tile_rows : 0;
     int tot_t, tot_v;
     const int excl = carry_t + block_exclusive_scan(cnt, wave_tot, &tot_t);
     const int v0 = carry_v + block_exclusive_scan(m, wave_tot, &tot_v);
@@ -140,6 +116,7 @@ __global__ __launch_bounds__(1024) void prefill_tiles_kernel(const int32_t* __re
     mtile_start[n_units] = carry_t;
     vstart[n_units] = carry_v;
   }
+  if (threadIdx.x < kQueueInts) queue[threadIdx.x] = 0;
 }
 
 // Row tables of a launch over several chunks: block (c, u) writes the
@@ -166,63 +143,11 @@ __global__ __launch_bounds__(256) void prefill_rows_kernel(const int32_t* __rest
 }
 
 // The tiles workspace: mtile_start [n_units+1], vstart [n_units+1] (each
-// padded to 16 bytes), desc [max_mtiles]; with several chunks also row_pos
+// padded to 16 bytes), queue [kQueueInts], desc [max_mtiles]; with several chunks also row_pos
 // and row_tok [rows] each.
 size_t tiles_index_bytes(int64_t n_units) { return ((size_t)(n_units + 1) * sizeof(int32_t) + 15) & ~(size_t)15; }
-size_t tiles_desc_offset(int64_t n_units) { return 2 * tiles_index_bytes(n_units); }
-
-// LDS byte offset of 16-byte chunk c (0..7) of row `row` in a 128-byte-row
-// tile.  gfx950's LDS serves 256 bytes per clock (64 four-byte banks), so
-// two consecutive 128-byte rows share one bank row; the chunk index is
-// XOR-ed with (row / 2) % 8, so the 16 rows that a quarter-wave b128 read
-// touches fill all 16 sixteen-byte bank slots (measured on gfx950: about
-// 195 B/clk per CU this way, 122 with the chunk XOR-ed by row % 8, whose
-// rows r and r + 8 collide, and 32 unswizzled).
-__device__ __forceinline__ int swz(int row, int c) { return row * kLdsRow + ((c ^ ((row >> 1) & 7)) << 4); }
-
-__device__ __forceinline__ v16f mfma_f8_32x32x64(const v8i& a, const v8i& b, const v16f& c) {
-  // Scale operands 0: the compiler emits the unscaled v_mfma_f32_32x32x64_f8f6f4
-  // (e4m3 operands, no block scales; see mfma_f8_16x16x128).
-  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
-}
-
-// The tile of work item `item`: expert u owns items [mtile_start[u],
-// mtile_start[u+1]) * n_tiles, in bands of kBand consecutive m-tiles, each
-// band n-tile major: item = mtile_start[u] * n_tiles + kBand * n_tiles *
-// band + nt * width + (mt - kBand * band) (width = the band's m-tiles; an
-// expert with at most kBand m-tiles is one band).  The m-tiles that read the
-// same weight slice (same nt) are neighbours, so they run together on one
-// XCD and the slice comes from HBM once per band (m-tile major order
-// fetched the weights once per m-tile); and an expert with many m-tiles
-// re-reads its token rows once per band pass instead of once per n-tile
-// (one n-tile-major pass over 141 m-tiles evicts them from L2 before the
-// next n-tile reads them again).  The expert's ceil(M/32) row groups are dealt evenly over its
-// mcount tiles (tile mt gets q/mcount groups, one more for mt < q % mcount):
-// the same MFMA work as full tiles plus a tail, but tiles of similar size,
-// which advance through their shared weight slice at similar speed, so the
-// slice is fetched from HBM once and read by the others from L2 (a 1-32-row
-// tail tile ran about 3.6 times faster than the full tiles and fetched the
-// slice ahead of them; gate/up read 1.7 times its algorithmic bytes).
-struct Tile {
-  int e, m0, mc, nt;  // expert, first row (a sorted position, or a launch row with row tables), rows, n-tile
-};
-
-__device__ __forceinline__ Tile tile_of(const PrefillArgs& p, int item) {
-  const int4 d = p.desc[item / p.n_tiles];
-  const int e = d.x, s0 = d.y, o0 = d.z, o1 = d.w;
-  const int mcount = (o1 - o0 + kBM - 1) / kBM;
-  const int local = item - s0 * p.n_tiles;
-  const int band = local / (kBand * p.n_tiles);
-  const int bw = min(kBand, mcount - band * kBand);
-  const int in_band = local - band * kBand * p.n_tiles;
-  const int ntx = in_band / bw;
-  const int mt = band * kBand + (in_band - ntx * bw);
-  const int q = (o1 - o0 + 31) >> 5;
-  const int base = q / mcount, extra = q - base * mcount;
-  const int first = o0 + 32 * (mt * base + min(mt, extra));
-  const int groups = base + (mt < extra ? 1 : 0);
-  return Tile{e, first, min(32 * groups, o1 - first), ntx};
-}
+size_t tiles_queue_offset(int64_t n_units) { return 2 * tiles_index_bytes(n_units); }
+size_t tiles_desc_offset(int64_t n_units) { return tiles_queue_offset(n_units) + kQueueInts * sizeof(int32_t); }
 
 template <bool GATEUP>
 __global__ __launch_bounds__(kThreads) void ffn_prefill_kernel(PrefillArgs p) {
@@ -236,16 +161,8 @@ __global__ __launch_bounds__(kThreads) void ffn_prefill_kernel(PrefillArgs p) {
   const int r32 = lane & 31;  // operand row (A) / column (B) of this lane
   const int g2 = lane >> 5;   // K half of a 64-K MFMA slice this lane supplies
 
-  // XCD-major work item over the real items (the grid is an upper bound):
-  // XCD x takes items [x*per, (x+1)*per) in order.
-  int total = p.mtile_start[p.n_units];
-  if (total > p.max_mtiles) total = (int)p.max_mtiles;  // inconsistent offsets: only described m-tiles run
-  const int real = total * p.n_tiles;  // < 2^31 (the grid bound is checked on the host)
-  const int per = (real + kXcd - 1) / kXcd;
-  const int slot = blockIdx.x / kXcd;
-  if (slot >= per) return;
-  const int item = (int)(blockIdx.x % kXcd) * per + slot;
-  if (item >= real) return;
+  const int item = prefill_item(p);
+  if (item < 0) return;
   const Tile tile = tile_of(p, item);  // one uniform load, no search and no barrier
   const int m0 = tile.m0;  // first sorted row of the tile
   const int mc = tile.mc;  // rows in the tile
@@ -719,15 +636,17 @@ moe_status_t run_ffn_prefill_view(const moe_dims_t& d, const PrefillRows& r, con
                 r.n_units, r.n_chunks);
   if (r.n_chunks > 65535 || r.n_units > 65535)
     return fail(MOE_ERR_UNSUPPORTED_SHAPE, "ffn_prefill: %d chunks x %d experts", r.n_chunks, r.n_units);
+  const int tile_rows = prefill_tile_rows(d, r, sx);
   uint8_t* tb = reinterpret_cast<uint8_t*>(tiles);
   int32_t* vstart = reinterpret_cast<int32_t*>(tb + tiles_index_bytes(r.n_units));
+  int32_t* queue = reinterpret_cast<int32_t*>(tb + tiles_queue_offset(r.n_units));
   int4* desc = reinterpret_cast<int4*>(tb + tiles_desc_offset(r.n_units));
   int32_t* row_pos = nullptr;
   int32_t* row_tok = nullptr;
   moe_status_t st = MOE_OK;
   if (!r.tiles_ready) {
     MOE_LAUNCH("prefill_tiles", prefill_tiles_kernel, dim3(1), dim3(1024), 0, stream, r.offsets, r.off_stride,
-               r.n_units, r.n_chunks, tiles, vstart, desc, r.max_mtiles);
+               r.n_units, r.n_chunks, tiles, vstart, queue, desc, r.max_mtiles, tile_rows);
     st = check_launch("prefill_tiles");
     if (st != MOE_OK) return st;
   }
@@ -744,27 +663,43 @@ moe_status_t run_ffn_prefill_view(const moe_dims_t& d, const PrefillRows& r, con
   PrefillArgs g{};
   g.a = qx; g.sa = sx; g.sorted_src = sorted_src; g.row_pos = row_pos; g.row_tok = row_tok;
   g.topk = d.topk; g.a_rows = r.tokens;
-  g.mtile_start = tiles; g.desc = desc; g.max_mtiles = r.max_mtiles; g.n_units = r.n_units;
+  g.mtile_start = tiles; g.desc = desc; g.max_mtiles = r.max_mtiles; g.n_units = r.n_units; g.tile_rows = tile_rows;
+  g.queue = queue;
   g.w0 = w_gate; g.s0 = s_gate; g.w1 = w_up; g.s1 = s_up;
   g.N = d.inter; g.K = d.hidden; g.n_tiles = d.inter / kBlock;
   g.qh = qh; g.sh = sh; g.y = nullptr;
-  st = launch_prefill<true>(g, r.max_mtiles, stream);
+  st = tile_rows == kBM ? launch_prefill<true>(g, r.max_mtiles, stream)
+                        : launch_prefill_wide(true, g, r.max_mtiles, stream);
   if (st != MOE_OK) return st;
 
   PrefillArgs dn{};
   dn.a = qh; dn.sa = sh; dn.sorted_src = nullptr; dn.row_pos = row_pos; dn.row_tok = nullptr;
   dn.topk = d.topk; dn.a_rows = (int)r.rows;
   dn.mtile_start = tiles; dn.desc = desc; dn.max_mtiles = r.max_mtiles; dn.n_units = r.n_units;
+  dn.tile_rows = tile_rows; dn.queue = queue;
   dn.w0 = w_down; dn.s0 = s_down; dn.w1 = nullptr; dn.s1 = nullptr;
   dn.N = d.hidden; dn.K = d.inter; dn.n_tiles = d.hidden / kBN;
   dn.y = y_rows; dn.qh = nullptr; dn.sh = nullptr;
-  return launch_prefill<false>(dn, r.max_mtiles, stream);
+  return tile_rows == kBM ? launch_prefill<false>(dn, r.max_mtiles, stream)
+                          : launch_prefill_wide(false, dn, r.max_mtiles, stream);
+}
+
+// The rows of a resident layer: one chunk of all its experts.
+static PrefillRows resident_rows(const moe_dims_t& d, int32_t T, const int32_t* offsets) {
+  PrefillRows r{};
+  r.offsets = offsets; r.n_units = d.n_experts; r.n_chunks = 1; r.tokens = T;
+  r.rows = r.unit_rows = (int64_t)T * d.topk;
+  r.max_mtiles = prefill_max_mtiles(r.rows, d.n_experts);
+  return r;
 }
 
 // The m-tile table inside a resident layer's tiles workspace.
-TilesOut prefill_tiles_out(const moe_dims_t& d, int32_t T, int32_t* tiles) {
-  return TilesOut{tiles, reinterpret_cast<int4*>(reinterpret_cast<uint8_t*>(tiles) + tiles_desc_offset(d.n_experts)),
-                  prefill_max_mtiles((int64_t)T * d.topk, d.n_experts)};
+TilesOut prefill_tiles_out(const moe_dims_t& d, int32_t T, const float* sx, int32_t* tiles) {
+  uint8_t* tb = reinterpret_cast<uint8_t*>(tiles);
+  return TilesOut{tiles, reinterpret_cast<int32_t*>(tb + tiles_queue_offset(d.n_experts)),
+                  reinterpret_cast<int4*>(tb + tiles_desc_offset(d.n_experts)),
+                  prefill_max_mtiles((int64_t)T * d.topk, d.n_experts),
+                  prefill_tile_rows(d, resident_rows(d, T, nullptr), sx)};
 }
 
 moe_status_t run_ffn_prefill(const moe_dims_t& d, int32_t T, const uint8_t* qx, const float* sx,
@@ -772,10 +707,7 @@ moe_status_t run_ffn_prefill(const moe_dims_t& d, int32_t T, const uint8_t* qx, 
                              const float* s_gate, const uint8_t* w_up, const float* s_up, const uint8_t* w_down,
                              const float* s_down, float* y_rows, uint8_t* qh, float* sh, int32_t* tiles,
                              bool tiles_ready, hipStream_t stream) {
-  PrefillRows r{};
-  r.offsets = offsets; r.off_stride = 0; r.n_units = d.n_experts; r.n_chunks = 1; r.chunk_rows = 0;
-  r.chunk_tokens = 0; r.tokens = T; r.rows = (int64_t)T * d.topk;
-  r.max_mtiles = prefill_max_mtiles(r.rows, d.n_experts);
+  PrefillRows r = resident_rows(d, T, offsets);
   r.tiles_ready = tiles_ready;
   return run_ffn_prefill_view(d, r, qx, sx, sorted_src, w_gate, s_gate, w_up, s_up, w_down, s_down, y_rows, qh, sh,
                               tiles, stream);

@@ -175,7 +175,7 @@ __device__ __forceinline__ void write_offsets(ChunkMasks& cm, int E, int first, 
   if (e < E) offsets[e] = first;
   if (e == 0) offsets[E] = total_valid;
   if (!tiles.mtile_start) return;
-  const int cnt = e < E ? (count + kPrefillTileRows - 1) / kPrefillTileRows : 0;
+  const int cnt = e < E ? (count + tiles.tile_rows - 1) / tiles.tile_rows : 0;
   int total;
   const int excl = block_exclusive_scan(cnt, cm.wave_tot, &total);
   if (e < E) {
@@ -184,6 +184,7 @@ __device__ __forceinline__ void write_offsets(ChunkMasks& cm, int E, int first, 
       tiles.desc[b] = make_int4(e, excl, first, first + count);
   }
   if (e == 0) tiles.mtile_start[E] = total;
+  if (e < kQueueInts) tiles.queue[e] = 0;
 }
 
 // One chunk (T <= 256): mask, scan and scatter in one workgroup.

@@ -316,6 +316,7 @@ extern "C" moe_status_t moe_ffn_streamed(moe_dims_t d, int32_t T, int32_t chunk_
         rows.chunk_tokens = (int)L.chunk;
         rows.tokens = T;
         rows.rows = (int64_t)T * k;
+        rows.unit_rows = rows.rows * g_here / E;
         rows.max_mtiles = (rows.rows + 127) / 128 + g_here;
         const moe_dims_t vd{d.hidden, d.inter, g_here, d.topk};
         st = run_ffn_prefill_view(vd, rows, qx, sx, sorted_src, ring_gate + slot0 * wmat, ring_sgate + slot0 * smat,
