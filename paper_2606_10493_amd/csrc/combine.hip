@@ -2,62 +2,82 @@
 // router weights in fp32, in slot order from +0.0, then rounded once to bf16
 // (the paper's router-weighted F32 accumulation followed by conversion back
 // to the hidden type).  Products and sums are rounded separately (FMA
-// contraction is switched off in combine8_batched), which is the exact order of the
+// contraction is switched off in add_slots), which is the exact order of the
 // definition, so the result is bit-identical to it for given rows.
 //
 // Memory bound: k * 4 bytes read + 2 bytes written per output element.
-// Thread = 8 consecutive outputs (two 16-byte loads per slot, one 16-byte
-// store); workgroup = 128 threads = 1024 outputs of one token.  Measured at
-// 5.1 TB/s on 8192 tokens x 8 slots (1.88 GB of rows read).
+// Thread = 4 consecutive outputs (one 16-byte load per slot, one 8-byte
+// store), so that a wave reads whole 1 KB pieces of a row; workgroup = 256
+// threads = 1024 outputs of one token.  The rows are read once and are mostly
+// larger than the caches, so the loads are non-temporal.  That needs whole
+// pieces and no row read twice: with 8 outputs per thread (two loads half a
+// KB apart by lane) non-temporal loads were slower than plain ones, and
+// reloading a slot in place of those past k (as plain loads did, from L1)
+// took 24.7 instead of 15.1 us at k = 2.
+// Measured (rocprofv3, before -> now): H 7168, k 8: 201 tokens 10.8 -> 9.8 us,
+// 1023 tokens 47.4 -> 43.8, 8192 tokens 385 -> 348 us (5.7 TB/s of rows and
+// outputs); H 2048, k 8: 3000 tokens 32.1 -> 32.2 (cached), 8000 tokens 120 ->
+// 89.5; H 4096, k 2: 2000 tokens 14.9 -> 14.2, 8000 tokens 72.1 -> 49.7 us.
 #include "common.h"
 
 namespace moe {
 namespace {
 
-// Slots in batches of 8: the batch's row indices and weights are loaded
-// first, then its 8 rows (16 loads in flight per thread), then the products
-// are added in slot order.  A slot past k reloads slot k-1 and is not
-// added.  Same arithmetic and order as combine8_of (the fused decode
-// kernel's combine), so the same bits.
-__device__ __forceinline__ uint4 combine8_batched(const float* __restrict__ y, const int32_t* __restrict__ dest,
-                                                  const float* __restrict__ w, int k, int H, int64_t t, int n) {
+// Slots j0 .. j0 + N - 1 added to acc: their row indices and weights are
+// loaded first, then the N rows (N loads in flight per thread), then the
+// products are added in slot order.
+template <int N>
+__device__ __forceinline__ void add_slots(float (&acc)[4], const float* __restrict__ y,
+                                          const int32_t* __restrict__ dest, const float* __restrict__ w, int H,
+                                          int n) {
 #pragma clang fp contract(off)
-  float acc[8];
+  int64_t p[N];
+  float wj[N];
+  v4f v[N];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) acc[i] = 0.0f;
-  for (int j0 = 0; j0 < k; j0 += 8) {
-    int64_t p[8];
-    float wj[8], v[8][8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int j = min(j0 + u, k - 1);
-      p[u] = dest[t * k + j];
-      wj[u] = w[t * k + j];
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) load8_f32(y + p[u] * H + n, v[u]);
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (j0 + u < k) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = acc[i] + wj[u] * v[u][i];
-      }
+  for (int u = 0; u < N; ++u) {
+    p[u] = dest[u];
+    wj[u] = w[u];
   }
-  uint4 o;
-  o.x = (uint32_t)f32_to_bf16_rne(acc[0]) | ((uint32_t)f32_to_bf16_rne(acc[1]) << 16);
-  o.y = (uint32_t)f32_to_bf16_rne(acc[2]) | ((uint32_t)f32_to_bf16_rne(acc[3]) << 16);
-  o.z = (uint32_t)f32_to_bf16_rne(acc[4]) | ((uint32_t)f32_to_bf16_rne(acc[5]) << 16);
-  o.w = (uint32_t)f32_to_bf16_rne(acc[6]) | ((uint32_t)f32_to_bf16_rne(acc[7]) << 16);
-  return o;
+#pragma unroll
+  for (int u = 0; u < N; ++u) v[u] = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(y + p[u] * H + n));
+#pragma unroll
+  for (int u = 0; u < N; ++u)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] = acc[i] + wj[u] * v[u][i];
 }
 
-__global__ __launch_bounds__(128) void combine_kernel(const float* __restrict__ y, const int32_t* __restrict__ dest,
+// Token t's outputs n .. n + 3: slots in batches of 8, then the remaining 0
+// to 7 in one batch of their own, so that no row is loaded twice.  Same
+// arithmetic and order as combine8_of (the fused decode kernel's combine), so
+// the same bits.
+__device__ __forceinline__ uint2 combine4_batched(const float* __restrict__ y, const int32_t* __restrict__ dest,
+                                                  const float* __restrict__ w, int k, int H, int64_t t, int n) {
+  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  dest += t * k;
+  w += t * k;
+  for (; k >= 8; k -= 8, dest += 8, w += 8) add_slots<8>(acc, y, dest, w, H, n);
+  switch (k) {
+    case 1: add_slots<1>(acc, y, dest, w, H, n); break;
+    case 2: add_slots<2>(acc, y, dest, w, H, n); break;
+    case 3: add_slots<3>(acc, y, dest, w, H, n); break;
+    case 4: add_slots<4>(acc, y, dest, w, H, n); break;
+    case 5: add_slots<5>(acc, y, dest, w, H, n); break;
+    case 6: add_slots<6>(acc, y, dest, w, H, n); break;
+    case 7: add_slots<7>(acc, y, dest, w, H, n); break;
+    default: break;
+  }
+  return make_uint2((uint32_t)f32_to_bf16_rne(acc[0]) | ((uint32_t)f32_to_bf16_rne(acc[1]) << 16),
+                    (uint32_t)f32_to_bf16_rne(acc[2]) | ((uint32_t)f32_to_bf16_rne(acc[3]) << 16));
+}
+
+__global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ y, const int32_t* __restrict__ dest,
                                                       const float* __restrict__ w, int k, int H, int blocks_per_tok,
                                                       uint16_t* __restrict__ out) {
   const int64_t t = blockIdx.x / blocks_per_tok;
-  const int n = ((int)(blockIdx.x - t * blocks_per_tok) * 128 + (int)threadIdx.x) * 8;
+  const int n = ((int)(blockIdx.x - t * blocks_per_tok) * 256 + (int)threadIdx.x) * 4;
   if (n >= H) return;
-  *reinterpret_cast<uint4*>(out + t * H + n) = combine8_batched(y, dest, w, k, H, t, n);
+  *reinterpret_cast<uint2*>(out + t * H + n) = combine4_batched(y, dest, w, k, H, t, n);
 }
 
 }  // namespace
@@ -76,7 +96,7 @@ extern "C" moe_status_t moe_combine(const float* y_rows, const int32_t* dest_row
   const int bpt = (H + 1023) / 1024;
   const int64_t blocks = (int64_t)T * bpt;
   if (blocks > 0x7fffffff) return fail(MOE_ERR_UNSUPPORTED_SHAPE, "moe_combine: too many tokens");
-  MOE_LAUNCH("combine", combine_kernel, dim3((unsigned)blocks), dim3(128), 0, stream, y_rows, dest_row, topk_w, k, H,
+  MOE_LAUNCH("combine", combine_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, y_rows, dest_row, topk_w, k, H,
                      bpt, out_bf16);
   return check_launch("moe_combine");
 }
