@@ -335,10 +335,11 @@ struct PrefillRows {
 // knows the experts' counts, or by prefill_tiles_kernel.
 constexpr int kPrefillTileRows = 128, kPrefillWideRows = 256;
 constexpr int kXcd = 8;
-constexpr int kQueueInts = 2 * kXcd;  // work-queue counters of the two GEMMs
+constexpr int kQueueInts = 2 * kXcd;  // work-queue counters of the two GEMMs, in the last entries of the descriptors
+constexpr int kQueueDescs = kQueueInts * sizeof(int32_t) / sizeof(int4);
 struct TilesOut {
   int32_t* mtile_start;  // [E+1]; NULL: no table wanted
-  int32_t* queue;        // [kQueueInts], zeroed
+  int32_t* queue;        // wide tiles: [kQueueInts], zeroed; else NULL
   int4* desc;            // [max_mtiles]
   int64_t max_mtiles;
   int tile_rows;         // kPrefillTileRows or kPrefillWideRows

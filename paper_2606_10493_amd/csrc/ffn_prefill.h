@@ -22,7 +22,7 @@ struct PrefillArgs {
   const int32_t* mtile_start; // [n_units+1] exclusive scan of the experts' m-tile counts
   const int4* desc;           // [max_mtiles] m-tile block descriptors (prefill_tiles_kernel)
   int64_t max_mtiles;         // bound on the m-tiles (sizes desc)
-  int32_t* queue;             // wide tiles: two sets of kXcd work-queue counters (gate/up, down), zeroed with the table
+  int32_t* queue;             // wide tiles: two sets of kXcd work-queue counters (gate/up, down), zeroed with the table; else NULL
   int tile_rows;              // expert rows per m-tile at most (kPrefillTileRows or kPrefillWideRows)
   int n_units;                // experts of the launch
   const uint8_t* w0;          // GATEUP: W_gate [E, N, K]; DOWN: W_down [E, N, K]; packed tiles

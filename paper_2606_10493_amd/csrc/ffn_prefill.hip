@@ -116,7 +116,7 @@ __global__ __launch_bounds__(1024) void prefill_tiles_kernel(const int32_t* __re
     mtile_start[n_units] = carry_t;
     vstart[n_units] = carry_v;
   }
-  if (threadIdx.x < kQueueInts) queue[threadIdx.x] = 0;
+  if (queue && threadIdx.x < kQueueInts) queue[threadIdx.x] = 0;
 }
 
 // Row tables of a launch over several chunks: block (c, u) writes the
@@ -143,11 +143,20 @@ __global__ __launch_bounds__(256) void prefill_rows_kernel(const int32_t* __rest
 }
 
 // The tiles workspace: mtile_start [n_units+1], vstart [n_units+1] (each
-// padded to 16 bytes), queue [kQueueInts], desc [max_mtiles]; with several chunks also row_pos
-// and row_tok [rows] each.
+// padded to 16 bytes), desc [max_mtiles]; with several chunks also row_pos and
+// row_tok [rows] each.  Wide tiles are half as many as the entries that
+// max_mtiles counts, and their queue counters take the last kQueueDescs of
+// them, so the workspace is the same for both (see desc_limit).
 size_t tiles_index_bytes(int64_t n_units) { return ((size_t)(n_units + 1) * sizeof(int32_t) + 15) & ~(size_t)15; }
-size_t tiles_queue_offset(int64_t n_units) { return 2 * tiles_index_bytes(n_units); }
-size_t tiles_desc_offset(int64_t n_units) { return tiles_queue_offset(n_units) + kQueueInts * sizeof(int32_t); }
+size_t tiles_desc_offset(int64_t n_units) { return 2 * tiles_index_bytes(n_units); }
+
+// Descriptors of a launch, and its queue counters behind them (NULL: none).
+int64_t desc_limit(int64_t max_mtiles, int tile_rows) {
+  return tile_rows == kPrefillWideRows ? max_mtiles - kQueueDescs : max_mtiles;
+}
+int32_t* queue_of(int4* desc, int64_t max_mtiles, int tile_rows) {
+  return tile_rows == kPrefillWideRows ? reinterpret_cast<int32_t*>(desc + desc_limit(max_mtiles, tile_rows)) : nullptr;
+}
 
 template <bool GATEUP>
 __global__ __launch_bounds__(kThreads) void ffn_prefill_kernel(PrefillArgs p) {
@@ -639,14 +648,15 @@ moe_status_t run_ffn_prefill_view(const moe_dims_t& d, const PrefillRows& r, con
   const int tile_rows = prefill_tile_rows(d, r, sx);
   uint8_t* tb = reinterpret_cast<uint8_t*>(tiles);
   int32_t* vstart = reinterpret_cast<int32_t*>(tb + tiles_index_bytes(r.n_units));
-  int32_t* queue = reinterpret_cast<int32_t*>(tb + tiles_queue_offset(r.n_units));
   int4* desc = reinterpret_cast<int4*>(tb + tiles_desc_offset(r.n_units));
+  const int64_t max_mtiles = desc_limit(r.max_mtiles, tile_rows);
+  int32_t* queue = queue_of(desc, r.max_mtiles, tile_rows);
   int32_t* row_pos = nullptr;
   int32_t* row_tok = nullptr;
   moe_status_t st = MOE_OK;
   if (!r.tiles_ready) {
     MOE_LAUNCH("prefill_tiles", prefill_tiles_kernel, dim3(1), dim3(1024), 0, stream, r.offsets, r.off_stride,
-               r.n_units, r.n_chunks, tiles, vstart, queue, desc, r.max_mtiles, tile_rows);
+               r.n_units, r.n_chunks, tiles, vstart, queue, desc, max_mtiles, tile_rows);
     st = check_launch("prefill_tiles");
     if (st != MOE_OK) return st;
   }
@@ -663,25 +673,25 @@ moe_status_t run_ffn_prefill_view(const moe_dims_t& d, const PrefillRows& r, con
   PrefillArgs g{};
   g.a = qx; g.sa = sx; g.sorted_src = sorted_src; g.row_pos = row_pos; g.row_tok = row_tok;
   g.topk = d.topk; g.a_rows = r.tokens;
-  g.mtile_start = tiles; g.desc = desc; g.max_mtiles = r.max_mtiles; g.n_units = r.n_units; g.tile_rows = tile_rows;
+  g.mtile_start = tiles; g.desc = desc; g.max_mtiles = max_mtiles; g.n_units = r.n_units; g.tile_rows = tile_rows;
   g.queue = queue;
   g.w0 = w_gate; g.s0 = s_gate; g.w1 = w_up; g.s1 = s_up;
   g.N = d.inter; g.K = d.hidden; g.n_tiles = d.inter / kBlock;
   g.qh = qh; g.sh = sh; g.y = nullptr;
-  st = tile_rows == kBM ? launch_prefill<true>(g, r.max_mtiles, stream)
-                        : launch_prefill_wide(true, g, r.max_mtiles, stream);
+  st = tile_rows == kBM ? launch_prefill<true>(g, max_mtiles, stream)
+                        : launch_prefill_wide(true, g, max_mtiles, stream);
   if (st != MOE_OK) return st;
 
   PrefillArgs dn{};
   dn.a = qh; dn.sa = sh; dn.sorted_src = nullptr; dn.row_pos = row_pos; dn.row_tok = nullptr;
   dn.topk = d.topk; dn.a_rows = (int)r.rows;
-  dn.mtile_start = tiles; dn.desc = desc; dn.max_mtiles = r.max_mtiles; dn.n_units = r.n_units;
+  dn.mtile_start = tiles; dn.desc = desc; dn.max_mtiles = max_mtiles; dn.n_units = r.n_units;
   dn.tile_rows = tile_rows; dn.queue = queue;
   dn.w0 = w_down; dn.s0 = s_down; dn.w1 = nullptr; dn.s1 = nullptr;
   dn.N = d.hidden; dn.K = d.inter; dn.n_tiles = d.hidden / kBN;
   dn.y = y_rows; dn.qh = nullptr; dn.sh = nullptr;
-  return tile_rows == kBM ? launch_prefill<false>(dn, r.max_mtiles, stream)
-                          : launch_prefill_wide(false, dn, r.max_mtiles, stream);
+  return tile_rows == kBM ? launch_prefill<false>(dn, max_mtiles, stream)
+                          : launch_prefill_wide(false, dn, max_mtiles, stream);
 }
 
 // The rows of a resident layer: one chunk of all its experts.
@@ -696,10 +706,10 @@ static PrefillRows resident_rows(const moe_dims_t& d, int32_t T, const int32_t* 
 // The m-tile table inside a resident layer's tiles workspace.
 TilesOut prefill_tiles_out(const moe_dims_t& d, int32_t T, const float* sx, int32_t* tiles) {
   uint8_t* tb = reinterpret_cast<uint8_t*>(tiles);
-  return TilesOut{tiles, reinterpret_cast<int32_t*>(tb + tiles_queue_offset(d.n_experts)),
-                  reinterpret_cast<int4*>(tb + tiles_desc_offset(d.n_experts)),
-                  prefill_max_mtiles((int64_t)T * d.topk, d.n_experts),
-                  prefill_tile_rows(d, resident_rows(d, T, nullptr), sx)};
+  int4* desc = reinterpret_cast<int4*>(tb + tiles_desc_offset(d.n_experts));
+  const PrefillRows r = resident_rows(d, T, nullptr);
+  const int tile_rows = prefill_tile_rows(d, r, sx);
+  return TilesOut{tiles, queue_of(desc, r.max_mtiles, tile_rows), desc, desc_limit(r.max_mtiles, tile_rows), tile_rows};
 }
 
 moe_status_t run_ffn_prefill(const moe_dims_t& d, int32_t T, const uint8_t* qx, const float* sx,

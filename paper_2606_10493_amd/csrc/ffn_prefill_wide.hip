@@ -462,12 +462,15 @@ static double tile_cost(const moe_dims_t& d, double mean_rows, double n_units, i
 // tokens x 2, 192 wide tiles against 288: 54 against 77 us; 2048 tokens, 288
 // against 480: 116 against 80 us, narrow tiles taken).
 // Shapes: row scales come four K blocks at a time (K a multiple of 512, sx
-// 16-byte aligned), 32-bit row offsets.
+// 16-byte aligned), 32-bit row offsets, and enough rows that the tile table,
+// sized for 128-row tiles, has room for the queue counters (about 1024).
 int prefill_tile_rows(const moe_dims_t& d, const PrefillRows& r, const float* sx) {
   const int step = kBlock * kScaleWin, kmax = kWideMaxBlocks * kBlock;
   if (d.hidden % step || d.inter % step || d.hidden > kmax || d.inter > kmax || !aligned(sx, 16) ||
       (int64_t)r.tokens * d.hidden > 0xffffffffll || r.rows * d.inter > 0xffffffffll || r.unit_rows < r.n_units)
     return kPrefillTileRows;
+  const int64_t wide_tiles = (r.rows + kPrefillWideRows - 1) / kPrefillWideRows + std::min<int64_t>(r.rows, r.n_units);
+  if (wide_tiles + kQueueDescs > r.max_mtiles) return kPrefillTileRows;
   const double mean = (double)r.unit_rows / r.n_units;
   return tile_cost(d, mean, r.n_units, kPrefillWideRows) < 0.99 * tile_cost(d, mean, r.n_units, kPrefillTileRows)
              ? kPrefillWideRows

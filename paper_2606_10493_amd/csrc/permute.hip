@@ -184,7 +184,7 @@ __device__ __forceinline__ void write_offsets(ChunkMasks& cm, int E, int first, 
       tiles.desc[b] = make_int4(e, excl, first, first + count);
   }
   if (e == 0) tiles.mtile_start[E] = total;
-  if (e < kQueueInts) tiles.queue[e] = 0;
+  if (tiles.queue && e < kQueueInts) tiles.queue[e] = 0;
 }
 
 // One chunk (T <= 256): mask, scan and scatter in one workgroup.
