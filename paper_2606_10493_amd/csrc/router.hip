@@ -25,6 +25,7 @@
 //     chosen experts; lanes 0 .. k-1 write ids and weights.
 #include "common.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace moe {
@@ -101,10 +102,11 @@ __global__ __launch_bounds__(256) void router_logits_kernel(const uint16_t* __re
 // 130 us (and one K slice instead of two, so half the partial logits).
 constexpr int kRtM = 128, kRtN = 256, kRtK = 64, kRtRow = 2 * kRtK;
 constexpr int kRtStages = 3;
+constexpr int64_t kRtMaxGridY = 65535;  // token tiles of one launch
 
 __global__ __launch_bounds__(512) void router_logits_tiled_kernel(const uint16_t* __restrict__ x, int T, int H,
                                                                   const uint16_t* __restrict__ w, int E, int kchunk,
-                                                                  float* __restrict__ part) {
+                                                                  int tile0, float* __restrict__ part) {
   constexpr int kStage = (kRtM + kRtN) * kRtRow;
   constexpr int kLoads = kStage / 1024 / 8;  // per wave and step, each 8 rows of 128 bytes
   __shared__ __attribute__((aligned(1024))) uint8_t smem[kRtStages * kStage];
@@ -112,7 +114,7 @@ __global__ __launch_bounds__(512) void router_logits_tiled_kernel(const uint16_t
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, kq = lane >> 4;
   const int wm = wave >> 2, wn = wave & 3;
-  const int ks = blockIdx.x, t0 = blockIdx.y * kRtM, e0 = blockIdx.z * kRtN;
+  const int ks = blockIdx.x, t0 = (tile0 + blockIdx.y) * kRtM, e0 = blockIdx.z * kRtN;
   const int64_t k0 = (int64_t)ks * kchunk;
   // Loader: load i of wave w takes stage rows 64 i + 8 w + [0, 8) (x rows 0 -
   // 127, then W_r rows; rows beyond T or E read a valid row), lane l the 16
@@ -599,9 +601,12 @@ extern "C" moe_status_t moe_router(const uint16_t* x_bf16, int32_t T, int32_t H,
   const int ks = router_slices(T, H, E);
   float* part = static_cast<float*>(ws);
   if (T >= kRouterTiledMinTokens) {
-    const dim3 grid((unsigned)ks, (unsigned)(((int64_t)T + kRtM - 1) / kRtM), (unsigned)((E + kRtN - 1) / kRtN));
-    MOE_LAUNCH("router_logits", router_logits_tiled_kernel, grid, dim3(512), 0, stream, x_bf16, T, H, w_router_bf16, E,
-               H / ks, part);
+    const int64_t tiles = ((int64_t)T + kRtM - 1) / kRtM;
+    for (int64_t t = 0; t < tiles; t += kRtMaxGridY) {
+      const dim3 grid((unsigned)ks, (unsigned)std::min(tiles - t, kRtMaxGridY), (unsigned)((E + kRtN - 1) / kRtN));
+      MOE_LAUNCH("router_logits", router_logits_tiled_kernel, grid, dim3(512), 0, stream, x_bf16, T, H, w_router_bf16, E,
+                 H / ks, (int)t, part);
+    }
   } else {
     const dim3 grid((unsigned)((T + 15) / 16), (unsigned)((E + 255) / 256), (unsigned)ks);
     MOE_LAUNCH("router_logits", router_logits_kernel, grid, dim3(256), 0, stream, x_bf16, T, H, w_router_bf16, E,

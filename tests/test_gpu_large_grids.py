@@ -24,3 +24,27 @@ def test_combine_of_more_than_2_24_workgroups(moe):
         b = min(t, a + (1 << 21))
         want = (w[a:b] * y[dest[a:b, 0].long()]).to(torch.bfloat16)  # one product, rounded in fp32 and once to bf16
         assert torch.equal(out[a:b], want.view(torch.int16)), a
+
+
+def test_router_of_more_than_65535_token_tiles(moe):
+    """128-token tiles lie along y: every token's result equals that of a call with fewer tokens."""
+    t, h, e = 65535 * 128 + 300, 32, 8
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn((t, h), generator=g, device="cuda").to(torch.bfloat16)
+    w = torch.randn((e, h), generator=g, device="cuda").to(torch.bfloat16)
+
+    def route(x):
+        ids = torch.full((len(x), 1), -1, dtype=torch.int32, device="cuda")
+        wts = torch.zeros((len(x), 1), device="cuda")
+        ws = torch.empty(moe.moe_router_workspace(len(x), h, e), dtype=torch.uint8, device="cuda")
+        ws.fill_(0xff)  # partial logits that a call leaves out are NaN
+        moe.moe_router(x, w, None, ids, wts, ws=ws)
+        return ids, wts
+
+    ids, wts = route(x)
+    assert int(ids.min()) >= 0
+    step = 1 << 20
+    for a in range(0, t, step):
+        b = min(t, a + step)
+        want = route(x[a:b])
+        assert torch.equal(ids[a:b], want[0]) and torch.equal(wts[a:b], want[1]), a
