@@ -102,7 +102,7 @@ __global__ __launch_bounds__(256) void router_logits_kernel(const uint16_t* __re
 // 130 us (and one K slice instead of two, so half the partial logits).
 constexpr int kRtM = 128, kRtN = 256, kRtK = 64, kRtRow = 2 * kRtK;
 constexpr int kRtStages = 3;
-constexpr int64_t kRtMaxGridY = 65535;  // token tiles of one launch
+constexpr int64_t kRtMaxGridY = 65535;  // token tiles of one launch (the device states 65536 blocks in y)
 
 __global__ __launch_bounds__(512) void router_logits_tiled_kernel(const uint16_t* __restrict__ x, int T, int H,
                                                                   const uint16_t* __restrict__ w, int E, int kchunk,

@@ -1,4 +1,5 @@
-"""Token counts whose one launch would pass a limit of the grid: 2^32 threads, 65535 blocks in y."""
+"""Token counts whose one launch would pass a limit of the grid: 2^32 threads (more are silently cut), and
+the 65536 blocks in y that the device states (this runtime runs more)."""
 import pytest
 import torch
 
