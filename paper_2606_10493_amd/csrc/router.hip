@@ -94,6 +94,10 @@ __global__ __launch_bounds__(256) void router_logits_kernel(const uint16_t* __re
 // fill all 64 banks (229 B/clk; c ^ row / 4 of a 64-byte row: 120).
 // The K slice is the fastest grid index: workgroups are dealt to the eight
 // XCDs in turn, so with 2, 4 or 8 slices an XCD's L2 holds one slice of W_r.
+// Up to kRtFewTiles token tiles the tile is: few tiles mean many short slices
+// (128 K, 256 bytes of a row), of which an XCD would load every eighth, that is
+// from few of its L2's channels (H 7168, E 256: 512 tokens 16.9 against 13.1
+// us, 640 tokens 15.1 against 13.0; 1024 tokens 14.1 against 15.7 the other way).
 // Loading x further ahead than W_r (separate waves, 4 + 3 and 5 + 2 stages) did
 // not help: 41 and 53 us at 8192 tokens.
 // Measured (rocprofv3, H 7168, E 256; before: 32-K tiles through a register
@@ -103,10 +107,12 @@ __global__ __launch_bounds__(256) void router_logits_kernel(const uint16_t* __re
 constexpr int kRtM = 128, kRtN = 256, kRtK = 64, kRtRow = 2 * kRtK;
 constexpr int kRtStages = 3;
 constexpr int64_t kRtMaxGridY = 65535;  // token tiles of one launch (the device states 65536 blocks in y)
+constexpr int kRtFewTiles = 6;
 
 __global__ __launch_bounds__(512) void router_logits_tiled_kernel(const uint16_t* __restrict__ x, int T, int H,
                                                                   const uint16_t* __restrict__ w, int E, int kchunk,
-                                                                  int tile0, float* __restrict__ part) {
+                                                                  int tile0, int tiles_first,
+                                                                  float* __restrict__ part) {
   constexpr int kStage = (kRtM + kRtN) * kRtRow;
   constexpr int kLoads = kStage / 1024 / 8;  // per wave and step, each 8 rows of 128 bytes
   __shared__ __attribute__((aligned(1024))) uint8_t smem[kRtStages * kStage];
@@ -114,7 +120,8 @@ __global__ __launch_bounds__(512) void router_logits_tiled_kernel(const uint16_t
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, kq = lane >> 4;
   const int wm = wave >> 2, wn = wave & 3;
-  const int ks = blockIdx.x, t0 = (tile0 + blockIdx.y) * kRtM, e0 = blockIdx.z * kRtN;
+  const int ks = tiles_first ? blockIdx.y : blockIdx.x, e0 = blockIdx.z * kRtN;
+  const int t0 = (tiles_first ? blockIdx.x : tile0 + blockIdx.y) * kRtM;
   const int64_t k0 = (int64_t)ks * kchunk;
   // Loader: load i of wave w takes stage rows 64 i + 8 w + [0, 8) (x rows 0 -
   // 127, then W_r rows; rows beyond T or E read a valid row), lane l the 16
@@ -602,10 +609,12 @@ extern "C" moe_status_t moe_router(const uint16_t* x_bf16, int32_t T, int32_t H,
   float* part = static_cast<float*>(ws);
   if (T >= kRouterTiledMinTokens) {
     const int64_t tiles = ((int64_t)T + kRtM - 1) / kRtM;
+    const bool tiles_first = tiles <= kRtFewTiles;
     for (int64_t t = 0; t < tiles; t += kRtMaxGridY) {
-      const dim3 grid((unsigned)ks, (unsigned)std::min(tiles - t, kRtMaxGridY), (unsigned)((E + kRtN - 1) / kRtN));
+      const unsigned n = (unsigned)std::min(tiles - t, kRtMaxGridY), ne = (unsigned)((E + kRtN - 1) / kRtN);
+      const dim3 grid = tiles_first ? dim3(n, (unsigned)ks, ne) : dim3((unsigned)ks, n, ne);
       MOE_LAUNCH("router_logits", router_logits_tiled_kernel, grid, dim3(512), 0, stream, x_bf16, T, H, w_router_bf16, E,
-                 H / ks, (int)t, part);
+                 H / ks, (int)t, (int)tiles_first, part);
     }
   } else {
     const dim3 grid((unsigned)((T + 15) / 16), (unsigned)((E + 255) / 256), (unsigned)ks);

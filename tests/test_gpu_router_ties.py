@@ -74,3 +74,22 @@ def test_tiled_logits_of_few_steps(moe, hidden, t):
     assert np.array_equal(ids[clear, :k], want_ids[clear])
     assert np.allclose(wts[clear, :k], want_w[clear], rtol=0, atol=1e-5 * 1.5)
     assert np.all(ids[:, k] == e) and np.all(wts[:, k] == 1.0)
+
+
+@pytest.mark.parametrize("t", [256, 768, 769])
+@pytest.mark.parametrize("e", [40, 300])
+def test_tiled_logits_around_the_tile_order(moe, t, e):
+    """Up to six 128-token tiles are the fastest grid index, beyond them the K slices; one and two expert tiles."""
+    rng = np.random.default_rng(e + t)
+    k = 4
+    x = synth.bf16_bits_from_f32(rng.integers(-4, 5, (t, 1024)).astype(np.float32) / 8)
+    wr = synth.bf16_bits_from_f32(rng.integers(-8, 9, (e, 1024)).astype(np.float32) / 64)
+    ids, wts = _route(moe, x, wr, None, k, 1, 1)
+    want_ids, want_w = ro.router(x, wr, None, k, 1, 1, 1.5)
+    # Exact logits (multiples of 2^-9 below 2^6); tokens whose rounded sigmoids are as close as above are left out.
+    s = np.sort(ro.router(x, wr, None, k, 1, 1, 1.5, want_intermediates=True)[2]["scores"], axis=1)[:, ::-1][:, :k + 1]
+    gap = s[:, :-1] - s[:, 1:]
+    clear = np.all((gap == 0) | (gap > 1e-6), axis=1)
+    assert clear.mean() > 0.5
+    assert np.array_equal(ids[clear], want_ids[clear])
+    assert np.allclose(wts[clear], want_w[clear], rtol=0, atol=1e-5 * 1.5)
