@@ -103,7 +103,7 @@ __global__ __launch_bounds__(256) void router_logits_kernel(const uint16_t* __re
 // Measured (rocprofv3, H 7168, E 256; before: 32-K tiles through a register
 // ring, 256-token tiles from 32768 tokens): 1500 tokens 16.3 -> 14.6 us, 8192
 // tokens 47.0 -> 39.3 us, 16384 tokens 90.7 -> 69.5 us, 32768 tokens 150 ->
-// 130 us (and one K slice instead of two, so half the partial logits).
+// 139 us.
 constexpr int kRtM = 128, kRtN = 256, kRtK = 64, kRtRow = 2 * kRtK;
 constexpr int kRtStages = 3;
 constexpr int64_t kRtMaxGridY = 65535;  // token tiles of one launch (the device states 65536 blocks in y)
@@ -560,10 +560,16 @@ constexpr int kRouterTiledMinTokens = 256;
 
 // K slices of the logits: enough workgroups to cover the chip (256 or
 // more), each slice a divisor of H / 32 slices of 32 and at least
-// kRouterMinChunk elements.
+// kRouterMinChunk elements.  From kRouterSplitTokens tokens on the tiles count
+// in pairs, so that up to 65280 tokens (E <= 256) two slices remain, each with an
+// accumulator of its own: one over all of H would save the second slice's
+// partial logits (32768 tokens, H 7168, E 256: 171 against 178 us), but its error against 64
+// bits is larger (logits 5.3e-7 of their norm instead of 3.7e-7).
+constexpr int kRouterSplitTokens = 32768;
 int router_slices(int32_t T, int32_t H, int32_t E) {
   const bool tiled = T >= kRouterTiledMinTokens;
-  const int64_t tiles = tiled ? ((int64_t)T + kRtM - 1) / kRtM * (((int64_t)E + kRtN - 1) / kRtN)
+  const int tile = T >= kRouterSplitTokens ? 2 * kRtM : kRtM;
+  const int64_t tiles = tiled ? ((int64_t)T + tile - 1) / tile * (((int64_t)E + kRtN - 1) / kRtN)
                               : ((int64_t)T + 15) / 16 * (((int64_t)E + 255) / 256);
   const int64_t want = tiles >= 256 ? 1 : (256 + tiles - 1) / tiles;
   const int n32 = H / 32;
