@@ -82,3 +82,51 @@ def test_layer_tiles_from_the_sort_equal_the_separate_calls(moe, t, zipf):
         outs.append(buf.out.cpu().numpy())
         assert int(buf.dev_status.item()) == 0
     assert np.array_equal(*outs)
+
+
+def _bad_ids(rng, t, k, e, share):
+    """Distinct ids, of which `share` become -1, e or above, or the token's first id."""
+    ids = _distinct_ids(rng, t, k, e)
+    how = rng.integers(0, 3, (t, k))
+    bad = np.where(how == 0, -1, np.where(how == 1, e + rng.integers(0, 9, (t, k)), ids[:, :1])).astype(np.int32)
+    return np.where(rng.random((t, k)) < share, bad, ids)
+
+
+@pytest.mark.parametrize("share", [0.01, 0.5, 1.0])
+@pytest.mark.parametrize("t,k,e", [(256, 32, 40), (200, 7, 1024), (700, 8, 64), (2049, 1, 5), (512 * 256 + 300, 2, 3)])
+def test_sort_parks_many_bad_slots(moe, t, k, e, share):
+    ids = _bad_ids(np.random.default_rng(t + k), t, k, e, share)
+    off, src, dst, _ = _permute(moe, ids, e)
+    valid = (ids >= 0) & (ids < e)
+    for j in range(1, k):
+        valid[:, j] &= np.all(ids[:, :j] != ids[:, j:j + 1], axis=1)
+    flat, good = ids.reshape(-1), np.flatnonzero(valid.reshape(-1))
+    want = np.concatenate([good[np.argsort(flat[good], kind="stable")], np.flatnonzero(~valid.reshape(-1))])
+    assert np.array_equal(src, want)
+    assert np.array_equal(dst[src], np.arange(t * k))
+    assert np.array_equal(off, np.searchsorted(np.sort(flat[good]), np.arange(e + 1)))
+
+
+@pytest.mark.parametrize("t,k,e", [(256, 32, 1024), (8192, 8, 256)])
+def test_bad_slots_are_not_walked_one_by_one(moe, t, k, e):
+    """A rank's ids of other ranks' experts are -1: they must not make the sort many times slower."""
+    ids = _distinct_ids(np.random.default_rng(0), t, k, e)
+    half = np.where(np.random.default_rng(1).random((t, k)) < 0.5, -1, ids).astype(np.int32)
+    times = []
+    for a in (ids, half):
+        d = to_dev(a)
+        off = torch.empty(e + 1, dtype=torch.int32, device="cuda")
+        src, dst = (torch.empty(t * k, dtype=torch.int32, device="cuda") for _ in range(2))
+        ws = torch.empty(moe.moe_permute_workspace(t, k, e), dtype=torch.uint8, device="cuda")
+        spans = []
+        for _ in range(12):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            for _ in range(10):
+                moe.moe_permute(d, e, off, src, dst, None, ws)
+            ev[1].record()
+            ev[1].synchronize()
+            spans.append(ev[0].elapsed_time(ev[1]))
+        times.append(min(spans))
+    # Measured: 9.5 -> 38 us and 10.5 -> 20 us; walked by one thread of each chunk 5590 and 486 us.
+    assert times[1] < 10 * times[0]
