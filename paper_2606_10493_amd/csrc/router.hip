@@ -441,10 +441,15 @@ __global__ __launch_bounds__(256) void router_select_kernel(const float* __restr
 
   if (k <= kArgmaxMaxK) {
     // Small k.  A key that is masked, taken or past E is 0, below the image of
-    // every float.  Lane j keeps slot j's expert.
+    // every float; a NaN is 1, the lowest of the kept (by its own image every
+    // token would choose an expert whose bias is a NaN).  Lane j keeps slot
+    // j's expert.
     uint32_t u[PER];
 #pragma unroll
-    for (int i = 0; i < PER; ++i) u[i] = lane + 64 * i < E && kept[i] ? ordered_bits(key[i]) : 0u;
+    for (int i = 0; i < PER; ++i) {
+      const uint32_t image = key[i] == key[i] ? ordered_bits(key[i]) : 1u;
+      u[i] = lane + 64 * i < E && kept[i] ? image : 0u;
+    }
     int my_e = 0;
     for (int j = 0; j < k; ++j) {
       uint32_t m = u[0];

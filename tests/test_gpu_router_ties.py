@@ -93,3 +93,27 @@ def test_tiled_logits_around_the_tile_order(moe, t, e):
     assert clear.mean() > 0.5
     assert np.array_equal(ids[clear], want_ids[clear])
     assert np.allclose(wts[clear], want_w[clear], rtol=0, atol=1e-5 * 1.5)
+
+
+@pytest.mark.parametrize("nan", [0x7fc00000, 0xffc00000], ids=["plus", "minus"])
+@pytest.mark.parametrize("t", [1, 70, 300])
+def test_nan_keys_come_last(moe, t, nan):
+    """An expert whose key is NaN (a NaN in its bias or router row, of either sign) is chosen by no token while
+    there are others; a token of NaNs takes the lowest experts, each once."""
+    rng = np.random.default_rng(t)
+    h, e, k, bad = 256, 70, 8, 66
+    x = rng.integers(-4, 5, (t, h)).astype(np.float32) / 8
+    wr = rng.integers(-8, 9, (e, h)).astype(np.float32) / 64
+    xb, wb = synth.bf16_bits_from_f32(x), synth.bf16_bits_from_f32(wr)
+    want, _ = ro.router(xb, np.delete(wb, bad, 0), None, k)
+    want = want + (want >= bad)
+    bias = np.zeros(e, np.float32)
+    bias.view(np.uint32)[bad] = nan
+    row = wb.copy()
+    row[bad, 3] = nan >> 16
+    for ids, wts in (_route(moe, xb, wb, bias, k, 1, 1), _route(moe, xb, row, None, k, 1, 1)):
+        assert np.array_equal(ids, want)
+        assert np.all(np.isfinite(wts))
+    xb[t // 2] = nan >> 16
+    ids, wts = _route(moe, xb, wb, None, k, 1, 1)
+    assert np.array_equal(ids[t // 2], np.arange(k)) and np.all(np.isnan(wts[t // 2]))
