@@ -38,7 +38,10 @@ constexpr int kDcMaxTokens = 16;              // rows of one expert: one 16-row 
 constexpr int kDcMaxK = 2048;                 // I
 constexpr int kDcQhBytes = kDcRows * kDcMaxK; // the quantized h rows in LDS: R * I at most
 constexpr int kDcSmallBytes = 32 * 1024;      // W_down bytes of a workgroup that are latency rather than streaming
-constexpr int kDcFullHidden = 4096;           // H / 16 workgroups fill the 256 CUs
+constexpr int kDcCus = 256;
+constexpr int kDcShortK = 512;                // I of a short expert
+constexpr int kDcLongRows = 18432;            // R * I of longer ones (18 x 1024, 24 x 768)
+constexpr int kDcUnevenRows = 20480;          // R * I of short ones, last round uneven (40 x 512)
 constexpr int kDcMaxExperts = 1024;          // four 256-expert chunks of offsets
 
 struct DownCombineArgs {
@@ -316,23 +319,33 @@ __global__ __launch_bounds__(64 * WAVES) void ffn_decode_down_combine_kernel(Dow
 
 }  // namespace
 
-// True when the fused down + combine takes this batch.  Against the separate
-// launches (quantize h, down, combine; rocprofv3, fused first):
-//   up to 16 rows always (the h rows of I <= 2048 fit in LDS);
-//   17 to 64 rows whose h rows fit in the same LDS, if the H / 16 workgroups
-//   fill the chip (H 4096, I 1536, 9 tokens x 2: 18.7 against 25.0 us; H 7168,
-//   I 1024, 3 x 8: 34.6 against 37.6) or have so little to stream that the
-//   launches are what counts (H 256, I 128, 16 x 2: 7.5 against 9.1 us, and
-//   two launches fewer for the host); not with half the CUs idle (H 2048, I
-//   768, 3 x 8: 18.0 against 15.6 us) or more to stream (H 1024, I 512, 16 x
-//   4: 14.9 against 11.8 us).
-// 2048-wide experts beyond 16 rows lose by the bytes: 32 rows 99 against 90 us.
+// True when the fused down + combine takes this batch.  Up to 16 rows always
+// (the h rows of I <= 2048 fit in LDS); 17 to 64 rows whose h rows fit in the same
+// LDS if
+//   the H / 16 workgroups fill the chip, for short experts (I <= 512), or for longer
+//   ones up to R * I = kDcLongRows; where their last round fills less than half of
+//   the CUs, only for short ones up to R * I = kDcUnevenRows; or
+//   a workgroup has so little to stream that the launches are what counts.
+// Every workgroup quantizes all R * I values of h itself, which the separate
+// launches do once, so larger ones lose.  Measured over H 4096 to 12288, I 256 to
+// 1792, 18 to 64 rows, uniform and skewed routing, whole layers, fused against
+// separate: I <= 512 0.77 - 0.97 of the time, R * I up to 18432 0.91 - 1.00, from
+// 23040 0.95 - 1.07.  H 4608 and 5120 (288 and 320 workgroups for 256 CUs): I <= 512
+// up to 20480 0.90 - 1.00, 24576 and more 0.98 - 1.04, longer experts 1.00 - 1.14.
+// H 256, I 128, 16 tokens x 2: 7.5 against 9.1 us and two launches fewer; with half
+// the CUs idle (H 2048, I 768, 3 x 8) 18.0 against 15.6 us, with more to stream
+// (H 1024, I 512, 16 x 4) 14.9 against 11.8 us.
 bool decode_down_combine_fits(const moe_dims_t& d, int32_t T) {
   const int64_t R = (int64_t)T * d.topk;
   if (T < 1 || T > kDcMaxTokens || R > kDcSmallRows || R * d.inter > kDcQhBytes || d.inter > kDcMaxK ||
       d.n_experts > kDcMaxExperts || d.hidden % 32)
     return false;
-  return R <= kDcRows || d.hidden >= kDcFullHidden || std::min<int64_t>(R, d.n_experts) * d.inter * 16 <= kDcSmallBytes;
+  if (R <= kDcRows || std::min<int64_t>(R, d.n_experts) * d.inter * 16 <= kDcSmallBytes) return true;
+  if (d.hidden < 16 * kDcCus) return false;
+  const int last = d.hidden / 16 % kDcCus;  // workgroups of the last round (0: a full one)
+  const bool even = last == 0 || 2 * last >= kDcCus;
+  if (d.inter <= kDcShortK) return even || R * d.inter <= kDcUnevenRows;
+  return even && R * d.inter <= kDcLongRows;
 }
 
 // y = down(h) of every active expert combined per token into out (bf16 [T, H]).

@@ -58,3 +58,31 @@ def test_small_layers_with_bad_ids(moe, h, i, e, k, t):
     assert sa == sb == moe.MOE_DEV_BAD_EXPERT_ID
     good = [tok for tok in range(t) if tok not in (1, 4)]
     assert np.array_equal(a[good], b[good])
+
+
+# (H, I, E, k, T) -> fused: edges of the rule beyond 16 rows.  H 5120 has 320 workgroups for 256 CUs.
+@pytest.mark.parametrize("h,i,e,k,t,fused", [
+    (256, 128, 8, 2, 16, True),     # 32 KB or less of W_down a workgroup
+    (2048, 768, 4, 2, 9, False),    # half the CUs idle
+    (4096, 512, 8, 4, 16, True),    # short experts up to 64 rows
+    (5120, 512, 8, 4, 16, False),   # uneven workgroups: up to R * I = 20480
+    (5120, 512, 8, 4, 10, True),
+    (4096, 1024, 4, 2, 9, True),    # R * I = 18432
+    (4096, 1024, 4, 4, 5, False),   # 20480
+    (6144, 768, 4, 2, 9, True),     # a last round of 128 workgroups
+    (5120, 768, 4, 2, 9, False),    # of 64
+    (5120, 1536, 4, 2, 9, False),
+    (5120, 1536, 4, 2, 8, True),    # 16 rows: always
+])
+def test_which_small_layers_are_fused(moe, h, i, e, k, t, fused):
+    def matrices(r, c):
+        return (torch.zeros((e, r, c), dtype=torch.uint8, device="cuda"),
+                torch.ones((e, r // 128, c // 128), dtype=torch.float32, device="cuda"))
+
+    ids = torch.arange(t * k, dtype=torch.int32, device="cuda").remainder(e).view(t, k)
+    buf = moe.MoELayerBuffers(h, i, e, k, t, moe.MOE_REGIME_DECODE, fused=True)
+    moe.moe_profile_begin(32)
+    moe.run_layer(buf, torch.zeros((t, h), dtype=torch.int16, device="cuda"), ids, torch.ones((t, k), device="cuda"),
+                  (*matrices(i, h), *matrices(i, h), *matrices(h, i)))
+    names = [name for name, _ in moe.moe_profile_end()]
+    assert ("ffn_decode_down_combine" in names) == fused and ("combine" in names) != fused
