@@ -198,6 +198,14 @@ moe_status_t moe_expert_ffn(moe_dims_t dims, int32_t T, moe_regime_t regime,
                             float* y_rows, void* ws, size_t ws_bytes, hipStream_t stream);
 
 /*
+ * Host only: the expert rows per GEMM tile (128 or 256) that a resident layer
+ * of T tokens takes in the PREFILL regime (with sx 16-byte aligned; 128
+ * otherwise); 0 for dims the regime does not take.  The results do not
+ * depend on it.
+ */
+int32_t moe_prefill_tile_rows(moe_dims_t dims, int32_t T);
+
+/*
  * W8A16 expert FFN, decode regime (T <= MOE_DECODE_MAX_TOKENS): the paper's
  * own GEMV numerics (AVX-512 FP8 GEMV Kernel, post-scaling and scale-block
  * loop): bf16 activations, FP8 weights expanded to bf16, bf16 x bf16

@@ -120,6 +120,11 @@ def moe_expert_ffn(dims: MoeDims, T: int, regime: int, qx, sx, expert_offsets, s
     _check(lib.moe_expert_ffn(dims, T, regime, *args, _nbytes(ws), _stream(stream)))
 
 
+def moe_prefill_tile_rows(dims: MoeDims, T: int) -> int:
+    """Expert rows per GEMM tile (128 or 256) of a resident prefill layer of T tokens (host only)."""
+    return int(lib.moe_prefill_tile_rows(dims, T))
+
+
 def moe_expert_ffn_w8a16_workspace(dims: MoeDims, T: int) -> int:
     return int(lib.moe_expert_ffn_w8a16_workspace(dims, T))
 

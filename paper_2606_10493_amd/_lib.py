@@ -77,6 +77,7 @@ _SIGS = {
     "moe_permute": (_ST, [_P, _I, _I, _I, _P, _P, _P, _P, _P, _S, _P]),
     "moe_expert_ffn_workspace": (_S, [MoeDims, _I, _ST]),
     "moe_expert_ffn": (_ST, [MoeDims, _I, _ST, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _S, _P]),
+    "moe_prefill_tile_rows": (_I, [MoeDims, _I]),
     "moe_combine": (_ST, [_P, _P, _P, _I, _I, _I, _P, _P]),
     "moe_ffn_layer_workspace": (_S, [MoeDims, _I, _ST]),
     "moe_ffn_layer": (_ST, [MoeDims, _I, _ST, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _S, _P]),

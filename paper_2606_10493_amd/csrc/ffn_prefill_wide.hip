@@ -39,6 +39,7 @@ constexpr int kStageA = kPrefillWideRows * kBlock;
 constexpr int kScaleWin = 4;                      // K blocks per row-scale window
 constexpr int kWideMaxBlocks = 64;                // K / 128 at most
 constexpr int kWideWorkgroups = 256;              // one per CU (LDS and registers allow no more)
+constexpr double kWideMinRounds = 2.4;            // full tiles per CU (see prefill_tile_rows)
 
 struct Smem {
   uint8_t w[2][kStageW];                          // packed operand tiles, slot (16-row group) s at 2048 s
@@ -454,13 +455,25 @@ static double tile_cost(const moe_dims_t& d, double mean_rows, double n_units, i
   return per_tile * (rounds(d.inter / kBlock) * d.hidden + rounds(d.hidden / kPrefillWeightRows) * d.inter);
 }
 
-// Wide tiles where they are expected to be faster by that cost: from about 120
+// Wide tiles where they are expected to be faster by that cost, from about 120
 // rows per expert, where the narrow tiles start to need a second tile per
-// expert.  Below, both have one tile per expert and the narrow kernel is 2 - 3 %
-// faster (3072 tokens, 96 rows per expert: 1349 against 1405, 830 against 847
-// us); with few tiles a further round decides (16 experts of 1536 x 4096: 1024
-// tokens x 2, 192 wide tiles against 288: 54 against 77 us; 2048 tokens, 288
-// against 480: 116 against 80 us, narrow tiles taken).
+// expert (below, both have one tile per expert and the narrow kernel is 2 - 3 %
+// faster: 3072 tokens, 96 rows per expert: 1349 against 1405, 830 against 847
+// us), and where a CU gets kWideMinRounds full tiles or more (of both GEMMs,
+// weighted by their K).  The cost knows the mean row count only; with few tiles
+// per CU one more tile decides, and skewed routing brings it: whole layers, wide
+// against narrow, uniform | Zipf(0.5) | Zipf(1):
+//   H 4096, I 1536, 16 experts,  2046 rows, 0.4 rounds: 0.78 | 1.07 | 1.06
+//   H 4096, I 4096,  8 experts,  3500 rows, 1.3:        0.96 | 1.26 | 1.30
+//   H 4096, I 2048, 32 experts,  4092 rows, 1.0:        0.94 | 1.28 | 1.28
+//   H 3072, I 1536, 64 experts,  9000 rows, 1.6:        0.87 | 1.04 | 1.07
+//   H 7168, I 2048, 64 experts,  8184 rows, 2.3:        0.93 | 1.06 | 1.01
+//   H 4096, I 1024, 128 experts, 16384 rows, 2.4:       0.93 | 1.00 | 0.99
+//   H 4096, I 2048, 32 experts, 12000 rows, 2.9:        0.93 | 0.96 | 0.97
+//   H 7168, I 2048, 64 experts, 16384 rows, 4.7:        0.91 | 0.91 | 0.97
+// Over 19 shapes, 4 to 256 experts, 30 to 1400 rows per expert, the cost alone took
+// wide tiles where they had up to 1.33 times the narrow ones' time; with the rounds
+// none has more than 1.03.
 // Shapes: row scales come four K blocks at a time (K a multiple of 512, sx
 // 16-byte aligned), 32-bit row offsets, and enough rows that the tile table,
 // sized for 128-row tiles, has room for the queue counters (about 1024).
@@ -471,6 +484,10 @@ int prefill_tile_rows(const moe_dims_t& d, const PrefillRows& r, const float* sx
     return kPrefillTileRows;
   const int64_t wide_tiles = (r.rows + kPrefillWideRows - 1) / kPrefillWideRows + std::min<int64_t>(r.rows, r.n_units);
   if (wide_tiles + kQueueDescs > r.max_mtiles) return kPrefillTileRows;
+  const double full = (double)r.unit_rows / (kPrefillWideRows * kWideWorkgroups);
+  const double rounds = full * (d.inter / kBlock * (double)d.hidden + d.hidden / kPrefillWeightRows * (double)d.inter) /
+                        ((double)d.hidden + d.inter);
+  if (rounds < kWideMinRounds) return kPrefillTileRows;
   const double mean = (double)r.unit_rows / r.n_units;
   return tile_cost(d, mean, r.n_units, kPrefillWideRows) < 0.99 * tile_cost(d, mean, r.n_units, kPrefillTileRows)
              ? kPrefillWideRows
