@@ -271,6 +271,8 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* wave_tot, int* t
 // with no registers in between.  The compiler does not track them (its own
 // builtin makes every later LDS read wait for all of them): a reader waits
 // with wait_async_and_barrier.  They count in vmcnt and complete in order.
+// They write m0, which is a reserved register that a clobber list cannot name:
+// the kernels that use them leave the compiler no use for it.
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }
