@@ -33,6 +33,8 @@ CFLAGS = [
     # Packed fp32 VALU forms are kept out of the generated code.
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
+    # A loop transformation that was asked for and not done is an error.
+    "-Werror=pass-failed",
     "-I", INCLUDE, "-I", CSRC,
 ]
 

@@ -25,10 +25,10 @@
 //
 // Latency is what limits a small GEMV, so the prologue before the first
 // weight load is short: every wave finds its expert with ballots over the
-// expert offsets (no LDS, no barrier), loads its token indices and then
-// issues a window of D K-blocks of weight fragments, gathered activation
-// fragments, weight scales and activation scales, all vector loads in one
-// in-order stream, so waiting for block j never waits for a later load.
+// expert offsets (no LDS, no barrier), issues its weight scales and token
+// indices and then its first K block of weights before it uses any of them.
+// From then on a wave has one K block in flight: the compiler does not unroll
+// the K loop (see there), and the other waves of the CU cover its round trips.
 //
 // W8A16 (A16): the paper's own GEMV numerics (AVX-512 FP8 GEMV Kernel,
 // post-scaling): bf16 activations, the FP8 weights expanded to bf16
@@ -140,7 +140,7 @@ __device__ __forceinline__ bf16x8 e4m3x8_to_bf16(int d0, int d1) {
   return bf16x8{a[0], a[1], b[0], b[1], c[0], c[1], e[0], e[1]};
 }
 
-template <int MT, int NT, bool GATEUP, bool QH, int U, bool A16 = false, bool X1 = false>
+template <int MT, int NT, bool GATEUP, bool QH, bool A16 = false, bool X1 = false>
 __global__ __launch_bounds__(256) void ffn_decode_kernel(DecodeArgs p) {
   static_assert(!QH || (!GATEUP && MT == 1), "QH is the down projection with at most 16 rows");
   static_assert(!(A16 && QH), "W8A16 reads bf16 h rows directly");
@@ -433,14 +433,14 @@ __global__ __launch_bounds__(256) void ffn_decode_kernel(DecodeArgs p) {
       };
 
       // K loop: block 0 was loaded above; each later block's loads are
-      // issued at the top of its iteration and the unrolled copies let the
-      // compiler hoist the next blocks' loads.
+      // issued at the top of its iteration.  (An unroll request is refused: the
+      // body has convergent matrix and lane instructions and the trip count is
+      // not a constant.)
       if (nkw > 0) {
         float ws[G];
         scales_of(0, ws);
         compute_block(kb0, wfirst, ws);
       }
-#pragma unroll U
       for (int j = 1; j < nkw; ++j) {
         const int bk = kb0 + kstride * j;
         v8i w[G][NT];
@@ -513,13 +513,13 @@ __global__ __launch_bounds__(256) void ffn_decode_kernel(DecodeArgs p) {
   }
 }
 
-template <int MT, int NT, bool GATEUP, bool QH, int U, bool A16 = false, bool X1 = false>
+template <int MT, int NT, bool GATEUP, bool QH, bool A16 = false, bool X1 = false>
 moe_status_t launch_decode(const DecodeArgs& a, int64_t max_items, hipStream_t stream) {
   const int64_t grid = max_items < 2048 ? max_items : 2048;
   if (grid <= 0) return MOE_OK;
   const char* name = A16 ? (GATEUP ? "ffn_decode_w8a16_gateup" : "ffn_decode_w8a16_down")
                          : (GATEUP ? "ffn_decode_gateup" : "ffn_decode_down");
-  MOE_LAUNCH(name, (ffn_decode_kernel<MT, NT, GATEUP, QH, U, A16, X1>), dim3((unsigned)grid), dim3(256), 0, stream,
+  MOE_LAUNCH(name, (ffn_decode_kernel<MT, NT, GATEUP, QH, A16, X1>), dim3((unsigned)grid), dim3(256), 0, stream,
              a);
   return check_launch(name);
 }
@@ -530,7 +530,7 @@ moe_status_t launch_decode(const DecodeArgs& a, int64_t max_items, hipStream_t s
 // that the many experts with few rows of a mixed batch run at the register
 // budget (and occupancy) of the one-operand kernel.  Each launch covers
 // only its experts; an expert has at most T rows.
-template <int NT, bool GATEUP, bool QH, int U1, int U24, bool A16 = false>
+template <int NT, bool GATEUP, bool QH, bool A16 = false>
 moe_status_t launch_by_rows(DecodeArgs a, int32_t T, int64_t R, int tiles_per_expert, hipStream_t stream) {
   auto items = [&](int lo) {  // experts with at least lo rows, at most E
     const int64_t n = R / lo;
@@ -538,15 +538,15 @@ moe_status_t launch_by_rows(DecodeArgs a, int32_t T, int64_t R, int tiles_per_ex
   };
   a.m_lo = 1;
   a.m_hi = 16;
-  moe_status_t st = launch_decode<1, NT, GATEUP, QH, U1, A16>(a, items(1), stream);
+  moe_status_t st = launch_decode<1, NT, GATEUP, QH, A16>(a, items(1), stream);
   if (st != MOE_OK || T <= 16) return st;
   a.m_lo = 17;
   a.m_hi = 32;
-  st = launch_decode<2, NT, GATEUP, false, U24, A16>(a, items(17), stream);
+  st = launch_decode<2, NT, GATEUP, false, A16>(a, items(17), stream);
   if (st != MOE_OK || T <= 32) return st;
   a.m_lo = 33;
   a.m_hi = 0x7fffffff;
-  return launch_decode<4, NT, GATEUP, false, U24, A16>(a, items(33), stream);
+  return launch_decode<4, NT, GATEUP, false, A16>(a, items(33), stream);
 }
 
 }  // namespace
@@ -573,7 +573,7 @@ moe_status_t run_ffn_decode_gateup(const moe_dims_t& d, int32_t T, const uint8_t
   g.offsets = offsets; g.E = d.n_experts;
   g.w0 = w_gate; g.s0 = s_gate; g.w1 = w_up; g.s1 = s_up;
   g.N = d.inter; g.K = d.hidden; g.out = h;
-  return launch_by_rows<1, true, false, 3, 2>(g, T, R, d.inter / 16, stream);
+  return launch_by_rows<1, true, false>(g, T, R, d.inter / 16, stream);
 }
 
 // One token without the layer prologue: the gate/up GEMV quantizes the bf16
@@ -594,7 +594,7 @@ moe_status_t run_ffn_decode_gateup_one_token(const moe_dims_t& d, const uint16_t
   g.x16 = x; g.ids = topk_ids; g.dev_status = dev_status; g.topk = d.topk; g.a_rows = 1; g.E = d.n_experts;
   g.w0 = w_gate; g.s0 = s_gate; g.w1 = w_up; g.s1 = s_up;
   g.N = d.inter; g.K = d.hidden; g.out = h;
-  return launch_decode<1, 1, true, false, 3, false, true>(g, (int64_t)d.topk * (d.inter / 16), stream);
+  return launch_decode<1, 1, true, false, false, true>(g, (int64_t)d.topk * (d.inter / 16), stream);
 }
 
 // Decode-regime FFN: gate/up -> h (fp32) -> quantize h -> down.
@@ -619,11 +619,11 @@ moe_status_t run_ffn_decode(const moe_dims_t& d, int32_t T, const uint8_t* qx, c
   if (T <= kQhRows && d.inter <= kQhMaxK) {
     dn.m_lo = 1;
     dn.m_hi = 0x7fffffff;
-    return launch_decode<1, 2, false, true, 4>(dn, dn_items, stream);
+    return launch_decode<1, 2, false, true>(dn, dn_items, stream);
   }
   st = moe_quant_rows_f32(h, (int32_t)R, d.inter, qh, sh, stream);
   if (st != MOE_OK) return st;
-  return launch_by_rows<2, false, false, 4, 2>(dn, T, R, d.hidden / 32, stream);
+  return launch_by_rows<2, false, false>(dn, T, R, d.hidden / 32, stream);
 }
 
 // W8A16 decode FFN: bf16 activations, gate/up -> h (bf16) -> down.
@@ -639,14 +639,14 @@ moe_status_t run_ffn_decode_w8a16(const moe_dims_t& d, int32_t T, const uint16_t
   g.offsets = offsets; g.E = d.n_experts;
   g.w0 = w_gate; g.s0 = s_gate; g.w1 = w_up; g.s1 = s_up;
   g.N = d.inter; g.K = d.hidden; g.out16 = h16;
-  moe_status_t st = launch_by_rows<1, true, false, 3, 2, true>(g, T, R, d.inter / 16, stream);
+  moe_status_t st = launch_by_rows<1, true, false, true>(g, T, R, d.inter / 16, stream);
   if (st != MOE_OK) return st;
   DecodeArgs dn{};
   dn.a16 = h16; dn.sorted_src = nullptr; dn.topk = d.topk; dn.a_rows = (int)R;
   dn.offsets = offsets; dn.E = d.n_experts;
   dn.w0 = w_down; dn.s0 = s_down;
   dn.N = d.hidden; dn.K = d.inter; dn.out = y_rows;
-  return launch_by_rows<2, false, false, 4, 2, true>(dn, T, R, d.hidden / 32, stream);
+  return launch_by_rows<2, false, false, true>(dn, T, R, d.hidden / 32, stream);
 }
 
 }  // namespace moe

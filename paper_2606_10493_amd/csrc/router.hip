@@ -59,7 +59,8 @@ __global__ __launch_bounds__(256) void router_logits_kernel(const uint16_t* __re
   v4f acc[4];
 #pragma unroll
   for (int nt = 0; nt < 4; ++nt) acc[nt] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
+  // One 32-K step at a time: the compiler refuses to unroll a loop of matrix
+  // instructions whose trip count is not a constant.
   for (int kk = 0; kk < kchunk; kk += 32) {
     const bf16x8 a = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(xa + kk));
 #pragma unroll
