@@ -377,8 +377,10 @@ __device__ __forceinline__ void wide_tile(const PrefillArgs p, Smem& sm, int ite
 // XCD's range and, once that is empty, of the other ranges in turn.  The ranges
 // keep an expert's items on one XCD's L2; the queues even out ranges of unequal
 // tiles (under skewed routing a range of full tiles takes several times as long
-// as a range of experts with a few rows).  The next item is asked for while the
-// tile runs.  A queue's counter only grows, so every workgroup ends: one that
+// as a range of experts with a few rows).  Wave 0 asks for the next item before
+// its tile and waits for the answer (one round trip, two or more once its own
+// range is empty), the other waves at the tile's first barrier; only the
+// hand-over through LDS is behind the tile.  A queue's counter only grows, so every workgroup ends: one that
 // finds nothing stops (another may still be taking the last items).
 typedef const __attribute__((address_space(4))) PrefillArgs KernArg;
 
