@@ -44,13 +44,14 @@ DEFAULT_ALSO = "prefill8k,decode64_zipf,decode4,decode1,decode1_w8a16,router"
 
 # HBM bytes moved by a kernel, from rocprofv3 FETCH_SIZE and WRITE_SIZE runs
 # scaled by a plain 1 GiB copy (FETCH x2.000, WRITE x1.000), recorded in the
-# profiles/ summaries of each workload.  Valid only while the kernel's source
-# file and the shared device header are the ones measured (sha256 prefix of
-# the two files' bytes, source first).  Decode entries are per step (all
-# launches of the kernel in a step), prefill entries per launch (the mean
+# profiles/ summaries of each workload.  Valid only while the sources that the
+# workload's launches of that kernel are compiled from are the ones measured
+# (sha256 prefix of the files' bytes in the order given).  Decode entries are per
+# step (all launches of the kernel in a step), prefill entries per launch (the mean
 # over the launches of a step), as the rooflines that carry them.
-_DEC, _PRE = "paper_2606_10493_amd/csrc/ffn_decode.hip", "paper_2606_10493_amd/csrc/ffn_prefill.hip"
-_COMMON = "paper_2606_10493_amd/csrc/common.h"
+_CSRC = "paper_2606_10493_amd/csrc/"
+_DEC = ("ffn_decode.hip", "common.h")
+_PRE = ("ffn_prefill.hip", "ffn_prefill_wide.hip", "ffn_prefill.h", "common.h")
 _DH, _PH = "cb7c22470036695c", "8d7be0b2719ce263"
 TRAFFIC = {
     ("decode1", "ffn_decode_gateup"): {"bytes": 235721523, "source": _DEC, "sha256_prefix": _DH},
@@ -64,11 +65,11 @@ TRAFFIC = {
 }
 
 
-def source_hash(source):
+def source_hash(files):
     import hashlib
     h = hashlib.sha256()
-    for f in (source, _COMMON):
-        with open(os.path.join(ROOT, f), "rb") as fh:
+    for f in files:
+        with open(os.path.join(ROOT, _CSRC, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
 

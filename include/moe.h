@@ -251,8 +251,9 @@ moe_status_t moe_combine(const float* y_rows, const int32_t* dest_row, const flo
  *   also write the prefill GEMMs' tile table (more than 64 slots, up to 131072
  *   tokens);
  *   DECODE regime with T * k <= 16 and I <= 2048 (or T <= 16, T * k <= 64 and
- *   small experts): the down projection and the combine run as one launch (a workgroup computes 16 output columns
- *   for every active expert and combines them per token in LDS);
+ *   small experts): the down projection and the combine run as one launch (a
+ *   workgroup computes 16 output columns for every active expert and combines
+ *   them per token in LDS);
  *   DECODE regime with T = 1, k <= 16, I <= 2048 and H <= 8192: two launches
  *   and no sort (one token's slots are distinct experts): the gate/up launch
  *   quantizes the token row itself and takes slot j's expert from topk_ids,

@@ -87,3 +87,19 @@ def test_streamed_bytes_follow_the_ring_schedule():
     one_gu, one_dn = bench.prefill_gemm_bytes(w, ids, [(0, w.n_experts)])
     gu, dn = bench.streamed_gemm_bytes(moe, w, ids, 1)
     assert dn == one_dn and gu >= one_gu and np.isclose(gu, one_gu, rtol=0.2)
+
+
+def test_recorded_traffic_is_keyed_on_every_source_of_its_kernels():
+    """A prefill launch runs one of two kernels: their two sources and their headers are all hashed, with the headers
+    that they include."""
+    import os
+    import re
+    for t in bench.TRAFFIC.values():
+        files = set(t["source"])
+        for f in t["source"]:
+            with open(os.path.join(bench.ROOT, bench._CSRC, f)) as fh:
+                files |= set(re.findall(r'#include "(\w+\.h)"', fh.read())) - {"moe.h"}
+        assert files == set(t["source"])
+        assert bench.source_hash(t["source"]) != bench.source_hash(t["source"][1:])
+    assert {f for (_, k), t in bench.TRAFFIC.items() if k.startswith("ffn_prefill") for f in t["source"]} == {
+        "ffn_prefill.hip", "ffn_prefill_wide.hip", "ffn_prefill.h", "common.h"}
