@@ -27,6 +27,19 @@ def test_combine_of_more_than_2_24_workgroups(moe):
         assert torch.equal(out[a:b], want.view(torch.int16)), a
 
 
+@pytest.mark.parametrize("t", [36800, 37000, 65000, 65200])
+def test_combine_on_both_sides_of_the_cached_rows(moe, t):
+    """Plain loads for 170 to 300 MB of rows, non-temporal ones below and beyond."""
+    h = 1152
+    assert (170e6 <= t * h * 4 <= 300e6) == (t in (37000, 65000))
+    y = torch.randn((t, h), device="cuda")
+    dest = torch.randperm(t, device="cuda").to(torch.int32)[:, None].contiguous()
+    w = torch.rand((t, 1), device="cuda") + 0.5
+    out = torch.empty((t, h), dtype=torch.int16, device="cuda")
+    moe.moe_combine(y, dest, w, out)
+    assert torch.equal(out, (w * y[dest[:, 0].long()]).to(torch.bfloat16).view(torch.int16))
+
+
 def test_router_of_more_than_65535_token_tiles(moe):
     """128-token tiles lie along y: every token's result equals that of a call with fewer tokens."""
     t, h, e = 65535 * 128 + 300, 32, 8
