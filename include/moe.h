@@ -200,8 +200,8 @@ moe_status_t moe_expert_ffn(moe_dims_t dims, int32_t T, moe_regime_t regime,
 /*
  * Host only: the expert rows per GEMM tile (128 or 256) that a resident layer
  * of T tokens takes in the PREFILL regime (with sx 16-byte aligned; 128
- * otherwise); 0 for dims the regime does not take.  The results do not
- * depend on it.
+ * otherwise); 0 for dims or token counts the regime does not take.  The
+ * results do not depend on it.
  */
 int32_t moe_prefill_tile_rows(moe_dims_t dims, int32_t T);
 

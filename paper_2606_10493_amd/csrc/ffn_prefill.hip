@@ -727,7 +727,7 @@ moe_status_t run_ffn_prefill(const moe_dims_t& d, int32_t T, const uint8_t* qx, 
 
 extern "C" int32_t moe_prefill_tile_rows(moe_dims_t d, int32_t T) {
   if (d.hidden <= 0 || d.inter <= 0 || d.inter % moe::kBlock || d.n_experts < 1 || d.topk < 1 || T < 0 ||
-      moe::prefill_shape_check(d) != MOE_OK)
+      (int64_t)T * d.topk > 0x7fffffff || moe::prefill_shape_check(d) != MOE_OK)
     return 0;
   return moe::prefill_tile_rows(d, moe::resident_rows(d, T, nullptr), nullptr);
 }

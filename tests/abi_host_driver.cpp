@@ -66,6 +66,7 @@ void workspace_queries() {
         sink ^= moe_ffn_layer_workspace(d, T, rg);
       }
       sink ^= moe_expert_ffn_w8a16_workspace(d, T);
+      sink ^= (size_t)moe_prefill_tile_rows(d, T);
       for (int32_t chunk : {-1, 0, 1, 256, 4096, INT32_MAX}) sink ^= moe_ffn_streamed_workspace(d, T, chunk);
     }
     for (int32_t H : {-1, 0, 32, 7168, INT32_MAX})

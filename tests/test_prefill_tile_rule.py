@@ -47,4 +47,5 @@ def test_query_of_dims_that_the_regime_does_not_take():
                  (65536, 512, 8, 2)):
         assert _rows(dims, 4096) == 0
     assert _rows(DEEPSEEK_V3, -1) == 0
+    assert _rows(DEEPSEEK_V3, 1 << 28) == 0  # 2^31 slots
     assert _rows(DEEPSEEK_V3, 0) == 128
