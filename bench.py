@@ -52,16 +52,16 @@ DEFAULT_ALSO = "prefill8k,decode64_zipf,decode4,decode1,decode1_w8a16,router"
 _CSRC = "paper_2606_10493_amd/csrc/"
 _DEC = ("ffn_decode.hip", "common.h")
 _PRE = ("ffn_prefill.hip", "ffn_prefill_wide.hip", "ffn_prefill.h", "common.h")
-_DH, _PH = "3b79c6ebf5e2a994", "0562055cc7bd387b"
+_DH, _PH = "3b79c6ebf5e2a994", "0b1433917e160e05"
 TRAFFIC = {
     ("decode1", "ffn_decode_gateup"): {"bytes": 235718861, "source": _DEC, "sha256_prefix": _DH},
     ("decode64_zipf", "ffn_decode_gateup"): {"bytes": 4603766989, "source": _DEC, "sha256_prefix": _DH},
     ("decode4", "ffn_decode_gateup"): {"bytes": 942058086, "source": _DEC, "sha256_prefix": _DH},
     ("decode1_w8a16", "ffn_decode_w8a16_gateup"): {"bytes": 235616461, "source": _DEC, "sha256_prefix": _DH},
-    ("prefill8k", "ffn_prefill_gateup"): {"bytes": 10753276006, "source": _PRE, "sha256_prefix": _PH},
-    ("prefill8k", "ffn_prefill_down"): {"bytes": 6241654579, "source": _PRE, "sha256_prefix": _PH},
-    ("prefill32k_streamed", "ffn_prefill_gateup"): {"bytes": 1464123802, "source": _PRE, "sha256_prefix": _PH},
-    ("prefill32k_streamed", "ffn_prefill_down"): {"bytes": 1010913485, "source": _PRE, "sha256_prefix": _PH},
+    ("prefill8k", "ffn_prefill_gateup"): {"bytes": 10643021005, "source": _PRE, "sha256_prefix": _PH},
+    ("prefill8k", "ffn_prefill_down"): {"bytes": 6232807834, "source": _PRE, "sha256_prefix": _PH},
+    ("prefill32k_streamed", "ffn_prefill_gateup"): {"bytes": 1464343040, "source": _PRE, "sha256_prefix": _PH},
+    ("prefill32k_streamed", "ffn_prefill_down"): {"bytes": 1010491187, "source": _PRE, "sha256_prefix": _PH},
 }
 
 
