@@ -8,6 +8,8 @@
 // written per element, + 4 bytes per 128 elements.
 //
 // Weights: one scale per 128x128 block; one 256-thread workgroup per block.
+#include <algorithm>
+
 #include "common.h"
 
 namespace moe {
@@ -75,8 +77,14 @@ moe_status_t quant_rows(const InT* x, int32_t rows, int32_t cols, uint8_t* q, fl
     return fail(MOE_ERR_INVALID_ARG, "%s: misaligned pointer", name);
   const int gpr = cols / kBlock;
   const int64_t n_groups = (int64_t)rows * gpr;
-  const int64_t blocks = (n_groups + 15) / 16;
-  MOE_LAUNCH(name, quant_rows_kernel<InT>, dim3((unsigned)blocks), dim3(256), 0, stream, x, n_groups, gpr, q, s);
+  // A grid has less than 2^32 threads (more are silently cut): whole rows of
+  // groups per launch, and their pointers.
+  const int64_t span_rows = std::max<int64_t>(1, (((int64_t)1 << 28) - 16) / gpr);
+  for (int64_t r0 = 0; r0 < rows; r0 += span_rows) {
+    const int64_t n = std::min(span_rows * gpr, n_groups - r0 * gpr);
+    MOE_LAUNCH(name, quant_rows_kernel<InT>, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, stream, x + r0 * cols, n, gpr,
+               q + r0 * cols, s + r0 * gpr);
+  }
   return check_launch(name);
 }
 

@@ -40,6 +40,22 @@ def test_combine_on_both_sides_of_the_cached_rows(moe, t):
     assert torch.equal(out, (w * y[dest[:, 0].long()]).to(torch.bfloat16).view(torch.int16))
 
 
+def test_quantization_of_2_35_values(moe):
+    """16 threads per 128 values: 2^32 threads and more.  104 GB, all ones: code 448 and scale 1 / 448."""
+    rows = (1 << 28) + 64
+    x = torch.full((rows, 128), 0x3f80, dtype=torch.int16, device="cuda")
+    q = torch.zeros((rows, 128), dtype=torch.uint8, device="cuda")
+    s = torch.zeros((rows, 1), device="cuda")
+    moe.moe_quant_act(x, q, s)
+    del x
+    one = torch.tensor(1.0) / torch.tensor(448.0)
+    for a in range(0, rows, 1 << 24):
+        assert bool((q[a:a + (1 << 24)] == 0x7e).all()), a
+    assert bool((s == one.item()).all())
+    del q, s
+    torch.cuda.empty_cache()
+
+
 def test_router_of_more_than_65535_token_tiles(moe):
     """128-token tiles lie along y: every token's result equals that of a call with fewer tokens."""
     t, h, e = 65535 * 128 + 300, 32, 8
